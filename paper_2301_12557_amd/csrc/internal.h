@@ -54,11 +54,11 @@ struct Item {
     uint32_t a_begin;   // first A point (sorted index)
     uint32_t b_begin;   // first B point
     uint32_t b_end;     // one past the last B point
-    uint32_t b_rowcell; // linear index of cell (x = 0) of the B row
-    uint32_t acnt_xb0;  // bits 0..15: A point count; bits 16..31: int16 unwrapped x of first B cell
+    uint32_t a_count;   // A points
     uint32_t meta;      // int8 dy | int8 dz << 8 | (sx+1) << 16 | (sy+1) << 18 | (sz+1) << 20 | flags << 24
     uint32_t cost;      // ordering key
-    uint32_t tile;      // A tile index (features, batched catalogue lookup)
+    uint32_t tile;      // A tile index (tree: A leaf)
+    uint32_t pad;
 };
 static_assert(sizeof(Item) == 32, "Item must be 32 bytes");
 
@@ -115,6 +115,12 @@ struct Plan {
     float r2prune32 = 0;        // FP32 candidate threshold (>= every relevant value)
     float d2small = 0;          // pairs closer than this are always rechecked (mu)
     float mu_tolA = 0, mu_tolB = 0, mu_tolC = 0;  // mu band: n*(A*rs + B*rs^2 + C)
+    // error of the kernel's first-axis squared separation, and of |pi| beside
+    // its relative rounding, which computed bins (uniform edges) allow for
+    ErrModel em1;
+    double e_pi = 0;
+    ErrModel tab1, tab2;        // error models and length of lut1 and lut2 (plan_short_tables)
+    int tab_log2 = 13;
     bool mu_top_closed = true;
     uint64_t id = 0;            // unique plan id (cells remember it)
     // stats of the last count
@@ -127,7 +133,6 @@ struct Plan {
     int64_t last_counts_n = 0;       // its entries when not nbins (triangle counts)
     void* timing_dev = nullptr;      // last recorded per-item times (u32) followed by the items
     uint32_t timing_n = 0;
-    int last_pts = 0;
     std::vector<char> host_stage;    // host copies of uploaded tables / kernel arguments
     std::vector<char> host_args;
     // learned cost model for FCFC_ORDER_LEARNED (not owned)
@@ -179,6 +184,8 @@ fcfc_status plan_finalize_grid(Plan* p);
 fcfc_status plan_finalize_numerics(Plan* p);
 int choose_k(const Plan* p, int64_t n_hint);
 int stencil_rows(const Plan* p, bool half, std::vector<int4>& rows);
+// Tables of half the length of lut1 and lut2 with the same bands.
+fcfc_status plan_short_tables(const Plan* p, Lut1D& t1, Lut1D& t2);
 // Table over the first-axis squared edges for binning values given in FP64:
 // its bands cover only the rounding of a value to FP32, so it depends on the
 // edges alone (no grid); built on first use and kept by the plan.

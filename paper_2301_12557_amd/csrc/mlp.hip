@@ -235,7 +235,7 @@ __global__ void k_item_features(const Item* __restrict__ items, const uint32_t* 
     uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const Item it = items[i];
-    const float na = (float)(it.acnt_xb0 & 0xffffu);
+    const float na = (float)it.a_count;
     const float nb = (float)(it.b_end - it.b_begin);
     const float dy = (float)(int8_t)(it.meta & 0xffu), dz = (float)(int8_t)((it.meta >> 8) & 0xffu);
     X[4 * (size_t)i + 0] = log2f(1.f + na);

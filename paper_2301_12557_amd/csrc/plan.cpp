@@ -258,6 +258,12 @@ fcfc_status plan_side_table(Plan* p, double e_axis, const Lut1D** out) {
     return FCFC_OK;
 }
 
+fcfc_status plan_short_tables(const Plan* p, Lut1D& t1, Lut1D& t2) {
+    FCFC_TRY(build_lut(t1, p->e1, p->tab1, p->tab_log2 - 1));
+    if (p->kind == FCFC_BIN_SPERP_PI) FCFC_TRY(build_lut(t2, p->e2, p->tab2, p->tab_log2 - 1));
+    return FCFC_OK;
+}
+
 fcfc_status plan_finalize_numerics(Plan* p) {
     const Grid& g = p->grid;
     const double u = U32;
@@ -282,6 +288,8 @@ fcfc_status plan_finalize_numerics(Plan* p) {
     p->has_big = false;
     p->lut1b = Lut1D();
     p->lut2b = Lut1D();
+    p->em1 = d2m;
+    p->e_pi = e;
     if (p->kind == FCFC_BIN_S || p->kind == FCFC_BIN_S_MU) {
         FCFC_TRY(build_lut(p->lut1, p->e1, d2m, lg));
         if (big) FCFC_TRY(build_lut(p->lut1b, p->e1, d2m, lg + 1));
@@ -328,7 +336,13 @@ fcfc_status plan_finalize_numerics(Plan* p) {
             m1.B += M * (d2m.A * sqrt(P2) + d2m.C * P2) +
                     M * ((2.0 * dpi * sqrt(P2) + dpi * dpi) * (1.0 + rel) + rel * P2);
             m1.C += M * u;
+            p->e_pi = dpi;
         }
+        p->em1 = p->tab1 = m1;
+        p->tab2 = m2;
+        // a computed bin squares |pi| = |dot| rsq(|l|^2), with twice the reciprocal's error
+        if (p->los == FCFC_LOS_MIDPOINT)
+            p->em1.B += 1.5 * (TRANS_REL + 6.0 * u) * (p->e2.back() * p->e2.back() * (1.0 + 1e-3) + 1.0);
         FCFC_TRY(build_lut(p->lut1, p->e1, m1, std::max(8, lg - 1)));
         FCFC_TRY(build_lut(p->lut2, p->e2, m2, std::max(8, lg - 1)));
         if (big) {

@@ -424,11 +424,11 @@ __global__ __launch_bounds__(256) void k_tree_items(TreeWL w, const uint32_t* __
                     it.a_begin = a0;
                     it.b_begin = s;
                     it.b_end = e;
-                    it.b_rowcell = s / (uint32_t)w.leafB;
-                    it.acnt_xb0 = a1 - a0;
+                    it.a_count = a1 - a0;
                     it.meta = meta0 | (same ? (ITEM_SAMEROW << 24) : 0u);
                     it.cost = (uint32_t)min<uint64_t>((uint64_t)(a1 - a0) * (e - s), 0xffffffffull);
                     it.tile = (uint32_t)ua;
+                    it.pad = 0;
                     items[at] = it;
                 }
             }

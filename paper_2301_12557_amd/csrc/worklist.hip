@@ -164,7 +164,6 @@ __device__ inline void tile_row_items(const Tile& tl, int4 srow, const uint32_t*
             if (hi < (double)(c1 + 1)) be = key_search(w.keyB, bb, be, base + (uint64_t)floor(hi * steps), true);
         }
         if (bb >= be) continue;
-        int xb0 = c0 + sx * w.nx;
         uint32_t meta = ((uint32_t)(uint8_t)(int8_t)dy) | ((uint32_t)(uint8_t)(int8_t)dz << 8) |
                         ((uint32_t)(sx + 1) << 16) | ((uint32_t)(sy + 1) << 18) | ((uint32_t)(sz + 1) << 20) |
                         (flags << 24);
@@ -173,14 +172,12 @@ __device__ inline void tile_row_items(const Tile& tl, int4 srow, const uint32_t*
             it.a_begin = tl.a_begin;
             it.b_begin = b;
             it.b_end = min(be, b + (uint32_t)w.bchunk);
-            it.b_rowcell = rowcell;
-            // the kernel walks B cells from the cell of the item's first point
-            const int xs = w.keyB ? (int)((w.keyB[b] >> w.xbits) - rowcell) + sx * w.nx : xb0;
-            it.acnt_xb0 = (tl.a_count & 0xffffu) | ((uint32_t)(uint16_t)(int16_t)xs << 16);
+            it.a_count = tl.a_count;
             it.meta = meta;
             uint64_t pairs = (uint64_t)tl.a_count * (uint64_t)(it.b_end - it.b_begin);
             it.cost = (uint32_t)min<uint64_t>(pairs, 0xffffffffull);
             it.tile = tile_id;
+            it.pad = 0;
             emit(it);
         }
     }

@@ -1,0 +1,122 @@
+"""The counting kernel at the edges of its tiles and of its choices: bit-exact against the oracle.
+
+The kernel takes 64 A points against groups of 16 staged B points (batches of
+64), computes bins where every axis has uniform edges and looks them up
+otherwise, and bounds the line-of-sight axis for (s_perp, pi).
+"""
+import numpy as np
+import pytest
+
+from helpers import check_case
+from paper_2301_12557_amd import fcfc, synth
+
+pytestmark = pytest.mark.gpu
+
+KINDS = [("s", "z", True), ("smu", "z", True), ("spi", "z", True), ("smu", "mid", False), ("spi", "mid", False)]
+
+
+def _edges(kind, smax, uniform, lo=0.0):
+    if uniform:
+        e1 = synth.linear_edges(lo, smax, 9)
+    else:
+        e1 = np.concatenate([[lo], np.geomspace(max(lo, 0.05) * 1.5, smax, 9)])
+    e2 = None
+    if kind == "smu":
+        e2 = synth.mu_edges(7)
+    elif kind == "spi":
+        e2 = synth.linear_edges(0, 0.8 * smax, 5) if uniform else np.array([0, 0.1, 0.25, 0.7]) * smax
+    return e1, e2
+
+
+@pytest.mark.parametrize("n1,n2", [(1, 1), (2, 15), (15, 16), (17, 63), (63, 64), (64, 65), (65, 79), (80, 81),
+                                   (127, 128), (128, 129), (129, 257), (193, 1025)])
+@pytest.mark.parametrize("kind,los,periodic", KINDS)
+def test_tile_and_group_remainders(kind, los, periodic, n1, n2):
+    rng = np.random.default_rng(n1 * 1000 + n2)
+    L = 40.0
+    off = 0.0 if periodic else 300.0
+    x1, x2 = rng.random((n1, 3)) * L + off, rng.random((n2, 3)) * L + off
+    w1, w2 = rng.uniform(0.5, 1.5, n1), rng.uniform(0.5, 1.5, n2)
+    box = L if periodic else 0.0
+    for uniform in (True, False):
+        e1, e2 = _edges(kind, 14.0, uniform)
+        kw = dict(kind=kind, edges1=e1, edges2=e2, los=los, box=box, cells_per_rmax=1)
+        check_case("cross", x1, x2, w1=w1, w2=w2, **kw)
+        check_case("auto", x2, w1=w2, **kw)
+        check_case("auto, unweighted", x2, **kw)
+
+
+@pytest.mark.parametrize("kind,los,periodic", KINDS)
+@pytest.mark.parametrize("n", [200, 3000])
+def test_thin_rows(kind, los, periodic, n):
+    """Tiles that span many cells: points thin along x (wide frames, wide boxes around the A points)."""
+    rng = np.random.default_rng(n)
+    x = rng.random((n, 3)) * np.array([3000.0, 60.0, 60.0]) + (0.0 if periodic else 400.0)
+    for uniform in (True, False):
+        e1, e2 = _edges(kind, 20.0, uniform, lo=2.0)
+        check_case("thin", x, kind=kind, edges1=e1, edges2=e2, los=los, box=3000.0 if periodic else 0.0,
+                   cells_per_rmax=1)
+
+
+@pytest.mark.parametrize("dist", [0.5, 5.0, 20.0, 60.0, 1000.0])
+@pytest.mark.parametrize("kind", ["smu", "spi"])
+def test_observer_distance(kind, dist):
+    """Mid-point line of sight from an observer inside the reach (where only the sphere filters) to far outside."""
+    rng = np.random.default_rng(int(dist * 10))
+    x = rng.random((700, 3)) * 50.0 + np.array([dist, -25.0, -25.0])
+    for uniform in (True, False):
+        e1, e2 = _edges(kind, 18.0, uniform)
+        check_case("observer", x[:300], x[300:], kind=kind, edges1=e1, edges2=e2, los="mid", box=0.0)
+
+
+@pytest.mark.parametrize("kind,los,periodic", KINDS)
+def test_duplicates_and_lattice(kind, los, periodic):
+    """Pairs at zero separation and on the edges themselves."""
+    g = np.stack(np.meshgrid(*[np.arange(8.0)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    x = np.concatenate([g, g[:100], g[:30]]) + (0.0 if periodic else 100.0)
+    e1 = np.arange(0.0, 4.0)
+    e2 = None if kind == "s" else synth.mu_edges(4) if kind == "smu" else np.arange(0.0, 3.0)
+    for k in (1, 3):
+        check_case("lattice", x, kind=kind, edges1=e1, edges2=e2, los=los, box=8.0 if periodic else 0.0,
+                   cells_per_rmax=k)
+
+
+@pytest.mark.parametrize("leaf", [32, 100, 128])
+@pytest.mark.parametrize("kind,los", [("s", "z"), ("smu", "mid"), ("spi", "mid"), ("spi", "z")])
+def test_tree_remainders(kind, los, leaf):
+    rng = np.random.default_rng(leaf)
+    for n1, n2 in ((5, 300), (129, 1000), (700, 65)):
+        x1, x2 = rng.random((n1, 3)) * 60.0 + 300.0, rng.random((n2, 3)) * 60.0 + 300.0
+        for uniform in (True, False):
+            e1, e2 = _edges(kind, 15.0, uniform)
+            check_case("tree", x1, x2, kind=kind, edges1=e1, edges2=e2, los=los, box=0.0, tree_leaf=leaf)
+
+
+@pytest.mark.parametrize("n", [100, 40_000])
+def test_work_list_lengths(n):
+    """Lists shorter than the device and much longer than it, whole and in shards."""
+    x = synth.uniform_box(n, 300.0, 3)
+    kw = dict(kind="s", edges1=synth.linear_edges(0, 30, 10), edges2=None, los="z", box=300.0)
+    check_case("list", x, method="grid", cells_per_rmax=1, **kw)
+    check_case("list, fine", x, method="grid", cells_per_rmax=6, b_chunk=256, **kw)
+
+
+@pytest.mark.parametrize("kind,los,periodic", [KINDS[1], KINDS[2], KINDS[4]])
+def test_largest_weighted_histograms(kind, los, periodic):
+    """The histogram sizes around the LDS limit: refused beyond the documented size, exact up to it."""
+    rng = np.random.default_rng(4)
+    x = rng.random((500, 3)) * 50.0 + (0.0 if periodic else 300.0)
+    w = rng.uniform(0.5, 1.5, 500)
+    taken = refused = 0
+    for n1 in (6480, 7000, 7080, 7120, 7160, 7200, 7240, 7400, 8000):
+        for uniform in (True, False):
+            m = n1 // 40  # bins of 20 / m on the first axis, 40 on the second
+            e1 = np.linspace(0, 20, m + 1) if uniform else 20.0 * np.linspace(0, 1, m + 1) ** 0.8
+            e2 = synth.mu_edges(40) if kind == "smu" else np.linspace(0, 10, 41) ** (1.0 if uniform else 1.1)
+            try:
+                check_case("large", x, kind=kind, edges1=e1, edges2=e2, los=los, box=50.0 if periodic else 0.0, w1=w)
+                taken += 1
+            except fcfc.FcfcError as e:
+                assert e.name in ("FCFC_ERANGE", "FCFC_EEDGES"), e
+                refused += 1
+    assert taken >= 4 and refused >= 2
