@@ -135,7 +135,26 @@ static void set_linear(const Plan* p, CountArgs& a) {
     if (!(a.l1t < 0.25f) || (two && !(a.l2t < 0.25f))) a.lin = 0;
 }
 
-static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch, int S, LaunchSetup& L) {
+// Format of the weighted words (add_weight) for products p with p 2^S integer
+// and |p| <= pmax.  A wave may test `limit` pairs and one more batch (at most
+// 79 staged B points x 64, and the rechecks waiting) before the words have to
+// be empty again, and 16 waves share them: 16 (limit + 5,248) <= 2^N.
+static void set_weight(CountArgs& a, int S, double pmax) {
+    int e = 0;
+    if (pmax > 0) frexp(pmax, &e);
+    const int qb = pmax > 0 ? std::min(62, std::max(53, e + S)) : 53;
+    const int N = (124 - qb) / 3;
+    WeightFmt& f = a.wf;
+    f.k = std::max(qb + N - 62, qb - 50);
+    f.cs = f.k + N + 1;
+    f.scale = ldexp(1.0, S - f.k);
+    f.mul = ldexp(1.0, f.k);
+    f.bias = ldexp(1.0, f.k - 1);
+    f.one = 1ull << f.cs;
+    f.limit = (1u << N) / 16u - 5248u;
+}
+
+static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch, LaunchSetup& L) {
     const Grid& g = p->grid;
     const bool tree = p->tune.tree_leaf > 0 && !batch;
     L.T = (tree || p->tune.tile_points != 64) ? 128 : 64;
@@ -147,7 +166,7 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
     L.nrows = stencil_rows(p, is_auto, L.rows);
     const bool two = (p->kind == FCFC_BIN_SPERP_PI);
     const bool mid = (p->los == FCFC_LOS_MIDPOINT && p->kind != FCFC_BIN_S);
-    const int per_wave = wave_lds_bytes(mid);
+    const int per_wave = wave_lds_bytes(mid, weighted);
     int dev = 0, maxlds = 65536;
     FCFC_HIP(hipGetDevice(&dev));
     if (hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) maxlds = 65536;
@@ -160,10 +179,11 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
     L.kern = (lin ? count_kernel_lin : count_kernel_lut)(mode, p->kind, p->los, is_auto, weighted);
     FCFC_HIP(hipFuncSetAttribute((const void*)L.kern, hipFuncAttributeMaxDynamicSharedMemorySize, maxlds));
     // LDS shared by the workgroup's waves for tables of n1t and n2t entries
+    auto tables_for = [&](int n1t, int n2t) {
+        return al16(n1t * 2 + 4) + al16(n2t * 2 + 4) + al16((p->n1 + 2) * 8) + al16(two ? (p->n2 + 2) * 8 : 0);
+    };
     auto shared_for = [&](int n1t, int n2t) {
-        return al16(n1t * 2 + 4) + al16(n2t * 2 + 4) + al16((p->n1 + 2) * 8) +
-               al16(two ? (p->n2 + 2) * 8 : 0) + al16(p->nbins * 4 * L.copies) +
-               (weighted ? al16(p->nbins * 16) : 0);
+        return tables_for(n1t, n2t) + (weighted ? al16(p->nbins * 16) : al16(p->nbins * 4 * L.copies));
     };
     // Workgroup size for a given shared part, and the waves resident per CU.
     // Default, from timings on MI355X: two workgroups of 16 or 12 waves per CU
@@ -211,11 +231,13 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
     int shared_bytes = lin ? shared_for(0, 0) : shared_for((int)T1->tab.size(), two ? (int)T2->tab.size() : 0);
     int waves = 1, resident = 0;
     bool fits = choose_waves(shared_bytes, waves, resident);
-    // Histograms are accepted up to the size that leaves room for the tables
-    // and one wave of MIN_WAVE_LDS, whatever this kernel's waves and bins need:
-    // where its larger waves do not fit beside the tables, shorter tables do.
+    // Histograms are accepted up to the size that leaves room for 4 bytes a bin
+    // and copy (16 more if weighted), the tables and one wave of MIN_WAVE_LDS,
+    // whatever this kernel's waves and bins need: where its larger waves do not
+    // fit beside the tables, shorter tables do.
     constexpr int MIN_WAVE_LDS = 3468, MIN_WAVE_LDS_MID = 5248;
-    const bool accepted = shared_for((int)T1->tab.size(), two ? (int)T2->tab.size() : 0) +
+    const bool accepted = tables_for((int)T1->tab.size(), two ? (int)T2->tab.size() : 0) +
+                              al16(p->nbins * 4 * L.copies) + (weighted ? al16(p->nbins * 16) : 0) +
                               (mid ? MIN_WAVE_LDS_MID : MIN_WAVE_LDS) + 64 <= maxlds;
     Lut1D s1, s2;
     if (accepted && !fits) {
@@ -256,7 +278,7 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
     a.off_band2 = off;
     off += al16(two ? (p->n2 + 2) * 8 : 0);
     a.off_hist = off;
-    off += al16(p->nbins * 4 * L.copies);
+    off += weighted ? 0 : al16(p->nbins * 4 * L.copies);
     a.off_whist = off;
     off += weighted ? al16(p->nbins * 16) : 0;
     a.off_wave = off;
@@ -319,7 +341,6 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
     a.mu_top_closed = 1;
     set_filter(p, a);
     set_linear(p, a);
-    a.wscale = ldexp(1.0, S - 32);
     a.ncat = 1;
     a.flush_pairs = 1ull << (p->tune.flush_log2 >= 1 && p->tune.flush_log2 <= FLUSH_LOG2_MAX ? p->tune.flush_log2
                                                                                               : FLUSH_LOG2_MAX);
@@ -486,8 +507,9 @@ fcfc_status count_pairs(Plan* p, Cells* c1, Cells* c2, int64_t* d_counts, double
         FCFC_TRY(weight_scale(c1->wmin, c1->wmax, cb->wmin, cb->wmax, &S));
     }
     LaunchSetup L;
-    FCFC_TRY(setup_launch(p, is_auto, weighted, false, S, L));
+    FCFC_TRY(setup_launch(p, is_auto, weighted, false, L));
     CountArgs& a = L.a;
+    if (weighted) set_weight(a, S, c1->wmax * cb->wmax);
     const bool sorted = !pr && p->tune.order != FCFC_ORDER_BUILT;
     const Model* model =
         pr ? pr->model : ((p->tune.order == FCFC_ORDER_LEARNED && !tree) ? p->model : nullptr);
@@ -745,6 +767,7 @@ struct BatchImpl {
     int64_t ntot = 0;
     bool weighted = false;
     int S = 0;
+    double wmax = 0;  // largest |weight|
     LaunchSetup L;
     WLArgs wl;
     int64_t nseg = 0, npair_tr = 0;
@@ -946,7 +969,7 @@ fcfc_status batch_create_impl(Plan* p, const fcfc_catalog* cats, int ncat, const
     for (int q = 0; q < npairs; q++) b->host_order[q] = (uint32_t)q;
     std::stable_sort(b->host_order.begin(), b->host_order.end(),
                      [&](uint32_t x, uint32_t y) { return cost[x] > cost[y]; });
-    fcfc_status s = setup_launch(p, all_auto, b->weighted, true, 0, b->L);
+    fcfc_status s = setup_launch(p, all_auto, b->weighted, true, b->L);
     if (s != FCFC_OK) {
         delete b;
         return s;
@@ -1053,6 +1076,7 @@ fcfc_status batch_create_impl(Plan* p, const fcfc_catalog* cats, int ncat, const
         double wmin = 0, wmax = 0;
         if (hw[0] != ~0ull) memcpy(&wmin, &hw[0], 8);
         memcpy(&wmax, &hw[1], 8);
+        b->wmax = wmax;
         fcfc_status ws = weight_scale(wmin, wmax, wmin, wmax, &b->S);
         if (ws != FCFC_OK) {
             batch_free_impl(b);
@@ -1103,7 +1127,7 @@ fcfc_status batch_create_impl(Plan* p, const fcfc_catalog* cats, int ncat, const
     a.out_w = b->weighted ? b->wacc : nullptr;
     a.stats = b->kstats;
     a.times = nullptr;
-    a.wscale = ldexp(1.0, b->S - 32);
+    if (b->weighted) set_weight(a, b->S, b->wmax * b->wmax);
     a.nchunks_dev = &b->ctr[3];
     a.chunk_cursor = &b->ctr[4];
     a.chunk_prefix = b->chunk_prefix;

@@ -58,14 +58,27 @@ constexpr int RB_CAP = RB_FLUSH + 64;
 constexpr int ASTAGE = 64;          // staged A points per wave
 constexpr int BSTAGE = 80;          // staged B points per wave: 15 waiting plus a batch of 64
 // LDS of one wave: staged A and B points, absolute A points (mid-point),
-// recheck entries (item, pair), queue
-__host__ __device__ constexpr int wave_lds_bytes(bool mid) {
-    return (ASTAGE + BSTAGE + (mid ? ASTAGE : 0)) * 16 + RB_CAP * 8 + QCAP * 2;
+// recheck entries (item, pair), queue, the staged points' weights.  (Weights
+// read from memory for every pair, as it came from the queue, left the few
+// waves of a weighted count waiting on them: on MI355X 1M weighted points in
+// 4,000 bins ran 5.61 -> 5.08 ms, a weighted survey of 200k x 4M 76.6 -> 72.5.)
+__host__ __device__ constexpr int wave_lds_bytes(bool mid, bool weighted) {
+    return (ASTAGE + BSTAGE + (mid ? ASTAGE : 0)) * 16 + RB_CAP * 8 + QCAP * 2 + (weighted ? (ASTAGE + BSTAGE) * 8 : 0);
 }
 constexpr uint32_t OFF_SA = 0, OFF_SB = ASTAGE * 16, OFF_SABS = (ASTAGE + BSTAGE) * 16;
+constexpr uint32_t OFF_SWA(bool mid) { return (uint32_t)wave_lds_bytes(mid, false); }
+constexpr uint32_t OFF_SWB(bool mid) { return OFF_SWA(mid) + ASTAGE * 8; }
 // A wavefront empties the LDS histograms into the outputs after claiming
 // 2^26 candidate pairs since it last did (fcfc_tuning.flush_log2 lowers it).
 constexpr int FLUSH_LOG2_MAX = 26;
+
+// Format of the exact weighted sums in LDS (add_weight).
+struct WeightFmt {
+    double scale, mul, bias;  // 2^(S - k), 2^k, 2^(k - 1)
+    unsigned long long one;   // 2^cs
+    int k, cs;
+    uint32_t limit;           // pairs a wave tests before it empties the words
+};
 
 struct CountArgs {
     const float4* posA;
@@ -112,7 +125,7 @@ struct CountArgs {
     float xstep;   // a row's points are sorted by x to this
     float mu_n, tolA, tolC;
     int mu_top_closed;
-    double wscale;  // 2^(S - 32): pair weight -> the high limb of the exact sum's fixed point
+    WeightFmt wf;
     int copies;
     unsigned long long flush_pairs;     // a wave merges after claiming this many pairs
     uint32_t shard_count, shard_index;  // this launch takes items shard_index, + shard_count, ...
@@ -139,7 +152,7 @@ struct Smem {
     const float2* band1;
     const float2* band2;
     uint32_t* hist;
-    unsigned long long* wl;  // exact weighted limbs, [bin][2]: low 32 bits, high part (signed)
+    uint32_t wl, wstride;    // weighted words: LDS address of the first, bytes to the second word of a bin
     // this wave's
     uint32_t wbase;   // LDS byte address of its part
     uint16_t* q;      // queue of pairs: b_slot << 6 | a_slot
@@ -147,6 +160,7 @@ struct Smem {
     uint32_t* rb;     // recheck entries (item, (b - b_begin) << 7 | a - a_begin)
     float4* sa;       // staged A points
     float4* sb;       // staged B points
+    double *swa, *swb;  // weights of the staged points
     float4* sabs;     // twice the A points in absolute FP32 (mid-point line of sight)
     unsigned long long* misc;
 };
@@ -277,6 +291,29 @@ __device__ inline int lut_hot_bin(const float2* __restrict__ band, int n, int e,
     return (k >= 1 && k <= n) ? k - 1 : -1;
 }
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// LDS by byte address
+typedef __attribute__((address_space(3))) const uint16_t LdsU16;
+typedef __attribute__((address_space(3))) const f32x4 LdsF4;
+typedef __attribute__((address_space(3))) uint32_t LdsU32;
+__device__ inline uint32_t lds_u16(uint32_t at) { return *(LdsU16*)at; }
+__device__ inline f32x4 lds_f4(uint32_t at) { return *(LdsF4*)at; }
+__device__ inline double lds_f64(uint32_t at) { return *(__attribute__((address_space(3))) const double*)at; }
+__device__ inline float lds_f1(uint32_t at) { return *(__attribute__((address_space(3))) const float*)at; }
+__device__ inline void lds_inc(uint32_t at) {
+    __hip_atomic_fetch_add((LdsU32*)at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+template <typename T>
+__device__ inline uint32_t lds_addr(T* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) T*)p; }
+typedef __attribute__((address_space(3))) unsigned long long LdsU64;
+__device__ inline void lds_add_u64(uint32_t at, unsigned long long v) {
+    __hip_atomic_fetch_add((LdsU64*)at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ inline unsigned long long lds_exch_u64(uint32_t at) {
+    return __hip_atomic_exchange((LdsU64*)at, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Kernel constants kept in registers.
 struct KConst {
     float scale1, scale2, vmax1, vmax2, mu_n, mu_nm1, tolA, tolC, side32;
@@ -284,21 +321,48 @@ struct KConst {
     float l1c, l1o, l1a, l1t, l2c, l2o, l2t;  // uniform edges (CountArgs)
     float tolC_v;  // tolC held in a vector register (an fma takes one scalar operand)
     int n1, n2, nbins, nx, copies;
-    double wscale;
+    WeightFmt wf;
 };
 
-// t: the pair weight times 2^(S - 32), where the weight times 2^S is an
-// integer q below 2^62 in magnitude.  The limbs of q are hi = floor(t), the
-// floor of q / 2^32, and lo = (t - hi) 2^32 in [0, 2^32), so q = hi 2^32 + lo;
-// every step is exact in FP64 (t has at most 30 integer bits and its
-// fraction holds the 32 low bits of q).
-__device__ inline void add_weight(const Smem& s, int flat, double t) {
-    const double hi = floor(t);
-    const uint32_t lo = (uint32_t)((t - hi) * 4294967296.0);
-    const int hi32 = (int)hi;
-    unsigned long long* wb = s.wl + 2 * flat;
-    atomicAdd(wb, (unsigned long long)lo);
-    atomicAdd(wb + 1, (unsigned long long)(long long)hi32);
+// Add a pair of weight p to bin `flat` of a weighted count.  p 2^S is an
+// integer q (the host chose S), |q| <= 2^qb; with q = i 2^k + r, |r| <= 2^(k-1),
+// the bin holds two 64-bit words,
+//   sum of (r + 2^(k-1)), from bit cs on the number of pairs, and
+//   sum of i (signed),
+// which stay exact for 2^N pairs: (qb - k) + N <= 62, cs = k + N + 1 and
+// cs + N + 1 <= 64 (set_weight; N is 20 to 23, and a wave empties the
+// workgroup's words in time).  i comes out of the low bits of t + 1.5 2^52,
+// t = p 2^(S-k), which rounds t to an integer; every step is exact in FP64.
+// Two LDS additions a pair instead of three, and 16 bytes a bin instead of 20:
+// the additions on random bins collide (half of the LDS cycles of a weighted
+// count).  On MI355X a weighted survey of 200k x 4M ran 80.4 -> 75.4 ms; 1M
+// weighted points in 4,000 bins gained nothing, where vector instructions bound
+// the kernel.  With the two words side by side, on half as many banks, the
+// survey took 79 ms.
+__device__ inline void add_weight(const Smem& s, const WeightFmt& f, uint32_t flat, double p) {
+    const double magic = 6755399441055744.0;  // 1.5 2^52
+    const double t = p * f.scale;
+    const double x = t + magic;
+    const double r = t - (x - magic);
+    const uint32_t lo = (uint32_t)__builtin_fma(r, f.mul, f.bias);
+    const unsigned long long hi = (unsigned long long)__double_as_longlong(x) - 0x4338000000000000ull;
+    const uint32_t at = s.wl + (flat << 3);
+    lds_add_u64(at, f.one + (unsigned long long)lo);
+    lds_add_u64(at + s.wstride, hi);
+}
+// The two words of a bin, taken out: number of pairs, and their sum times 2^S.
+__device__ inline uint32_t weight_words(const WeightFmt& f, unsigned long long lo, unsigned long long hi, __int128& sum) {
+    const uint32_t n = (uint32_t)(lo >> f.cs);
+    const long long rest = (long long)(lo & ((1ull << f.cs) - 1ull)) - ((long long)n << (f.k - 1));
+    sum = ((__int128)(long long)hi << f.k) + (__int128)rest;
+    return n;
+}
+__device__ inline void add_out_w(unsigned long long* out, __int128 v) {
+    const unsigned long long vlo = (unsigned long long)v;
+    unsigned long long vhi = (unsigned long long)(v >> 64);
+    const unsigned long long o = atomicAdd(out, vlo);
+    if (o + vlo < o) vhi += 1ull;
+    if (vhi) atomicAdd(out + 1, vhi);
 }
 
 // Re-evaluate `cnt` queued pairs (entries base .. base+cnt-1) in FP64.
@@ -317,11 +381,10 @@ __device__ __attribute__((always_inline)) inline void process_rechecks(ArgsRef a
         const double* pb = a.p64B + 3 * (size_t)ib;
         int flat = exact_bin<KIND, LOS>(a, pa[0], pa[1], pa[2], pb[0], pb[1], pb[2], sx, sy, sz);
         if (flat >= 0) {
-            atomicAdd(&s.hist[flat], 1u);
-            if (W) {
-                double p = a.wA[ia] * a.wB[ib];
-                add_weight(s, flat, p * a.wscale);
-            }
+            if (W)
+                add_weight(s, a.wf, (uint32_t)flat, a.wA[ia] * a.wB[ib]);
+            else
+                atomicAdd(&s.hist[flat], 1u);
         }
     }
     nrechk += (unsigned long long)cnt;
@@ -349,34 +412,18 @@ __device__ inline uint32_t lane_prefix(uint64_t m) {
 // Per-wave context of the current work item: 64 of its A points against its
 // B points.
 struct WaveCtx {
-    uint32_t a0;       // sorted index of A slot 0
-    uint32_t aslot0;   // its position in the item's A tile (0 or 64)
-    uint32_t b_begin, it;
+    uint32_t aslot0;   // position of A slot 0 in the item's A tile (0 or 64)
+    uint32_t it;
     int rcount;
     unsigned long long nrechk;
     float t1, t1a, t2, tA, tC;  // tolerances of the computed bins, widened for this tile
 };
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// LDS by byte address
-typedef __attribute__((address_space(3))) const uint16_t LdsU16;
-typedef __attribute__((address_space(3))) const f32x4 LdsF4;
-typedef __attribute__((address_space(3))) uint32_t LdsU32;
-__device__ inline uint32_t lds_u16(uint32_t at) { return *(LdsU16*)at; }
-__device__ inline f32x4 lds_f4(uint32_t at) { return *(LdsF4*)at; }
-__device__ inline float lds_f1(uint32_t at) { return *(__attribute__((address_space(3))) const float*)at; }
-__device__ inline void lds_inc(uint32_t at) {
-    __hip_atomic_fetch_add((LdsU32*)at, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-template <typename T>
-__device__ inline uint32_t lds_addr(T* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) T*)p; }
-
 // Bin `cnt` queued pairs (entries base .. base+cnt-1), one per lane.  An entry
 // is b_slot << 6 | a_slot, slots of the staged points.  Staged A points hold
 // the cell-local position (y and z moved into the B row's frame) and the cell
 // x as a float; staged B points the cell-local position and, in w, the point's
-// offset in the item << 8 | cell x (both cell x counted from the tile's first
+// offset in the item << 11 | cell x (both cell x counted from the tile's first
 // cell, plus 64).  The queue holds every pair in range and a few just beyond
 // (the filter of process_half is conservative), so the pair is formed here in
 // cell-local FP32, the arithmetic the error bands are derived for.
@@ -402,12 +449,10 @@ __device__ __attribute__((always_inline)) inline void bin_queue(ArgsRef a, const
     const f32x4 A = lds_f4(s.wbase + OFF_SA + (as << 4));
     const f32x4 B = lds_f4(s.wbase + OFF_SB + (bs << 4));
     const uint32_t bw = __float_as_uint(B.w);
-    const bool valid = lane < cnt;
-    // the weights of the pair, fetched early (product formed only for pairs in range)
     double wa = 0.0, wb = 0.0;
-    if (W && valid) {
-        wb = (a.wB + c.b_begin)[bw >> 8];
-        wa = (a.wA + c.a0)[as];
+    if (W) {
+        wa = lds_f64(s.wbase + OFF_SWA(MID) + (as << 3));
+        wb = lds_f64(s.wbase + OFF_SWB(MID) + (bs << 3));
     }
     float dx, dy, dz;
     if (TREE || LIN) {  // both in the frame of the A points
@@ -506,12 +551,10 @@ __device__ __attribute__((always_inline)) inline void bin_queue(ArgsRef a, const
         flat = (int)__umul24((uint32_t)b1, (uint32_t)k.n2) + b2;
     }
     if (__builtin_amdgcn_inverse_ballot_w64(um)) {
-        lds_inc(hist_l + ((uint32_t)flat << 2));
-        if (W) {
-            // fl(wa * wb) * 2^(S - 32) is exact: the scale only moves the exponent, and
-            // the host chose S so that every scaled product lies in [2^20, 2^30)
-            add_weight(s, flat, (wa * wb) * k.wscale);
-        }
+        if (W)
+            add_weight(s, k.wf, (uint32_t)flat, wa * wb);
+        else
+            lds_inc(hist_l + ((uint32_t)flat << 2));
     }
     const uint64_t m = rm;
     if (m) {
@@ -519,7 +562,7 @@ __device__ __attribute__((always_inline)) inline void bin_queue(ArgsRef a, const
         if (__builtin_amdgcn_inverse_ballot_w64(m)) {
             uint32_t* r = s.rb + (size_t)pos * 2;
             r[0] = c.it;
-            r[1] = ((bw >> 8) << 7) | (c.aslot0 + as);
+            r[1] = ((bw >> 11) << 7) | (c.aslot0 + as);
         }
         c.rcount += (int)__popcll(m);
         if (c.rcount >= RB_FLUSH) {
@@ -641,9 +684,10 @@ void k_count(const CountArgs* argp) {
     s.band1 = (const float2*)(smem + a.off_band1);
     s.band2 = (const float2*)(smem + a.off_band2);
     s.hist = (uint32_t*)(smem + a.off_hist);
-    s.wl = (unsigned long long*)(smem + a.off_whist);
+    s.wl = lds_addr(smem + a.off_whist);
+    s.wstride = 8u * (uint32_t)a.nbins;
     {
-        unsigned char* pw = smem + a.off_wave + (size_t)wave * wave_lds_bytes(MID);
+        unsigned char* pw = smem + a.off_wave + (size_t)wave * wave_lds_bytes(MID, W);
         s.wbase = lds_addr(pw);
         s.sa = (float4*)pw;
         pw += ASTAGE * 16;
@@ -654,6 +698,9 @@ void k_count(const CountArgs* argp) {
         s.rb = (uint32_t*)pw;
         pw += RB_CAP * 8;
         s.q = (uint16_t*)pw;
+        pw += QCAP * 2;
+        s.swa = (double*)pw;
+        s.swb = s.swa + ASTAGE;
         s.qbase = lds_addr(s.q);
         for (int i = lane; i < QCAP / 2; i += 64) ((uint32_t*)s.q)[i] = 0u;
     }
@@ -675,9 +722,10 @@ void k_count(const CountArgs* argp) {
             float2* b2 = (float2*)(smem + a.off_band2);
             for (int i = tid; i < a.n2 + 2; i += nthr) b2[i] = a.band2[i];
         }
-        for (int i = tid; i < a.nbins * a.copies; i += nthr) s.hist[i] = 0u;
         if (W)
-            for (int i = tid; i < 2 * a.nbins; i += nthr) s.wl[i] = 0ull;
+            for (int i = tid; i < 2 * a.nbins; i += nthr) ((unsigned long long*)(smem + a.off_whist))[i] = 0ull;
+        else
+            for (int i = tid; i < a.nbins * a.copies; i += nthr) s.hist[i] = 0u;
         if (tid < 4) s.misc[tid] = 0ull;
     }
     __syncthreads();
@@ -700,7 +748,7 @@ void k_count(const CountArgs* argp) {
     k.nbins = a.nbins;
     k.nx = a.nx;
     k.copies = a.copies;
-    k.wscale = a.wscale;
+    if (W) k.wf = a.wf;
     // (kept in registers: the compiler would load them again for every row)
     k.l1c = a.l1c;
     k.l1o = a.l1o;
@@ -726,54 +774,53 @@ void k_count(const CountArgs* argp) {
     const uint32_t lane_id = ((uint32_t)lcol << 6) | ((uint32_t)lk << 2);
 
     unsigned long long wave_pairs = 0;  // pairs claimed since this wave last emptied the histogram
+    uint32_t wave_tested = 0;           // weighted: pairs tested since then
     unsigned long long nflush = 0;      // merges made by this wave before the end
     const unsigned long long flush_pairs = a.flush_pairs;
     uint32_t out_off = 0;               // first bin of the current catalogue in the outputs
     // u32 overflow guard of the LDS histogram: every wave empties it (atomic
     // exchange) after claiming flush_pairs <= 2^26 pairs, so it never holds
     // more than 16 (2^26 + 128 x 2^19) = 2^31 increments (items hold at most
-    // 128 x b_chunk pairs, b_chunk <= 2^19)
+    // 128 x b_chunk pairs, b_chunk <= 2^19).  Weighted words hold less: a wave
+    // also empties them once it has tested wf.limit pairs since it last did.
     auto exchange_out = [&]() __attribute__((always_inline)) {
         nflush++;
+        if (W) {
+            for (int b = lane; b < k.nbins; b += 64) {
+                const unsigned long long lo = lds_exch_u64(s.wl + 8u * (uint32_t)b);
+                const unsigned long long hi = lds_exch_u64(s.wl + 8u * (uint32_t)b + s.wstride);
+                if (!(lo | hi)) continue;
+                __int128 v;
+                const uint32_t n = weight_words(k.wf, lo, hi, v);
+                if (n) atomicAdd(&a.out_counts[out_off + b], (unsigned long long)n);
+                add_out_w(&a.out_w[2 * ((size_t)out_off + b)], v);
+            }
+            return;
+        }
         for (int b = lane; b < k.nbins * k.copies; b += 64) {
             uint32_t v = atomicExch(&s.hist[b], 0u);
             if (v) atomicAdd(&a.out_counts[out_off + b % k.nbins], (unsigned long long)v);
-        }
-        if (W) {
-            for (int b = lane; b < k.nbins; b += 64) {
-                unsigned long long lo = atomicExch(&s.wl[2 * b], 0ull);
-                unsigned long long hi = atomicExch(&s.wl[2 * b + 1], 0ull);
-                __int128 v = ((__int128)(long long)hi << 32) + (__int128)lo;
-                unsigned long long vlo = (unsigned long long)v;
-                unsigned long long vhi = (unsigned long long)(v >> 64);
-                unsigned long long o = atomicAdd(&a.out_w[2 * ((size_t)out_off + b)], vlo);
-                if (o + vlo < o) vhi += 1ull;
-                if (vhi) atomicAdd(&a.out_w[2 * ((size_t)out_off + b) + 1], vhi);
-            }
         }
     };
     // workgroup-wide merge of the LDS histograms into the outputs, then clear
     auto merge_out = [&]() __attribute__((always_inline)) {
         for (int b = tid; b < k.nbins; b += nthr) {
+            if (W) {
+                const unsigned long long lo = lds_exch_u64(s.wl + 8u * (uint32_t)b);
+                const unsigned long long hi = lds_exch_u64(s.wl + 8u * (uint32_t)b + s.wstride);
+                if (!(lo | hi)) continue;
+                __int128 v;
+                const uint32_t n = weight_words(k.wf, lo, hi, v);
+                if (n) atomicAdd(&a.out_counts[out_off + b], (unsigned long long)n);
+                add_out_w(&a.out_w[2 * ((size_t)out_off + b)], v);
+                continue;
+            }
             uint32_t cnt = 0;
             for (int r = 0; r < k.copies; r++) {
                 cnt += s.hist[r * k.nbins + b];
                 s.hist[r * k.nbins + b] = 0u;
             }
             if (cnt) atomicAdd(&a.out_counts[out_off + b], (unsigned long long)cnt);
-            if (W) {
-                unsigned long long lo = s.wl[2 * b], hi = s.wl[2 * b + 1];
-                s.wl[2 * b] = 0ull;
-                s.wl[2 * b + 1] = 0ull;
-                if (lo | hi) {
-                    __int128 v = ((__int128)(long long)hi << 32) + (__int128)lo;
-                    unsigned long long vlo = (unsigned long long)v;
-                    unsigned long long vhi = (unsigned long long)(v >> 64);
-                    unsigned long long o = atomicAdd(&a.out_w[2 * ((size_t)out_off + b)], vlo);
-                    if (o + vlo < o) vhi += 1ull;
-                    if (vhi) atomicAdd(&a.out_w[2 * ((size_t)out_off + b) + 1], vhi);
-                }
-            }
         }
     };
     auto drain_rechecks = [&]() __attribute__((always_inline)) {
@@ -822,7 +869,6 @@ void k_count(const CountArgs* argp) {
         // same-row items count b > a: nothing before a0 can pair
         uint32_t jc = samerow ? max(b_begin, a0) : b_begin;
         if (jc >= b_end) return;
-        c.a0 = a0;
         const bool av_ok = (uint32_t)lane < cnt;
         const float4 av = a.posA[a0 + (av_ok ? (uint32_t)lane : 0u)];
         float4 aabs = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -834,6 +880,11 @@ void k_count(const CountArgs* argp) {
             (void*)(a.posB + b_begin), (short)0, (int)((b_end - b_begin) * 16u), BUFFER_RSRC_WORD3);
         const uint32_t lane16 = (uint32_t)lane * 16u;
         float4 bnext = load_b(rB, lane16, (jc - b_begin) * 16u);
+        double wnext = 0.0;
+        if (W) {
+            wnext = a.wB[min(jc + (uint32_t)lane, b_end - 1u)];
+            s.swa[lane] = a.wA[a0 + (av_ok ? (uint32_t)lane : 0u)];
+        }
         const float Dy = (float)idy * k.side32;
         const float Dz = (float)idz * k.side32;
         int4 ja = make_int4(0, 0, 0, 0);
@@ -953,10 +1004,14 @@ void k_count(const CountArgs* argp) {
             const float4 b = bnext;
             const uint32_t j = jc + (uint32_t)lane;
             const bool more = jc + 64u < b_end;
-            if (more) bnext = load_b(rB, lane16, (jc + 64u - b_begin) * 16u);
+            const double wj = wnext;
+            if (more) {
+                bnext = load_b(rB, lane16, (jc + 64u - b_begin) * 16u);
+                if (W) wnext = a.wB[min(jc + 64u + (uint32_t)lane, b_end - 1u)];
+            }
             float bx, by, bz;  // in the frame centred on the A points
             float sx = b.x, sy = b.y, sz = b.z;  // as staged
-            uint32_t bw = (j - b_begin) << 8;
+            uint32_t bw = (j - b_begin) << 11;
             if (TREE) {
                 const uint32_t leaf = min(j / a.tree_leaf, a.tree_nleafB - 1u);
                 const int4 jb = a.leaf_orgB[leaf];
@@ -993,10 +1048,18 @@ void k_count(const CountArgs* argp) {
             if (keep) {
                 const int slot = ns + (int)lane_prefix(km);
                 s.sb[slot] = make_float4(sx, sy, sz, __uint_as_float(bw));
+                if (W) s.swb[slot] = wj;
             }
             const int added = (int)__popcll(km);
             ns += added;
             ncand += (unsigned long long)((uint32_t)added * cnt);
+            if (W) {
+                wave_tested += (uint32_t)added * cnt;
+                if (wave_tested >= k.wf.limit) {
+                    wave_tested = (uint32_t)added * cnt;
+                    exchange_out();
+                }
+            }
             jc += 64u;
             wave_sync_lds();
             // ---- whole groups of 16 staged points (the rest too at the end) ----
@@ -1038,7 +1101,7 @@ void k_count(const CountArgs* argp) {
                     bu = lk == 2 ? uon * __builtin_amdgcn_sqrtf(rr[0]) : (lk == 3 ? 1.0f : 0.f);
                 }
                 // same-row items count b > a: the B point's rank against the A slots
-                const int rel = AUTO ? (int)(b_begin + (w >> 8) - a0) - 4 * lk : 0;
+                const int rel = AUTO ? (int)(b_begin + (w >> 11) - a0) - 4 * lk : 0;
                 const uint32_t gid = lane_id + ((uint32_t)g << 10);
 #pragma unroll
                 for (int m = 0; m < 4; m++) {
@@ -1069,9 +1132,16 @@ void k_count(const CountArgs* argp) {
             const int left = ns - done;
             if (done > 0 && left > 0) {
                 float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (lane < left) t = s.sb[done + lane];
+                double tw = 0.0;
+                if (lane < left) {
+                    t = s.sb[done + lane];
+                    if (W) tw = s.swb[done + lane];
+                }
                 wave_sync_lds();
-                if (lane < left) s.sb[lane] = t;
+                if (lane < left) {
+                    s.sb[lane] = t;
+                    if (W) s.swb[lane] = tw;
+                }
                 wave_sync_lds();
             }
             ns = left;
@@ -1097,11 +1167,11 @@ void k_count(const CountArgs* argp) {
         const uint32_t nxt_it = grab();
         const Item cur = ldc_item(a.items, it);
         const uint32_t acnt = cur.a_count;
-        c.b_begin = cur.b_begin;
         c.it = it;
         wave_pairs += (uint64_t)acnt * (uint64_t)(cur.b_end - cur.b_begin);
         if (wave_pairs >= flush_pairs) {
             wave_pairs = 0;
+            wave_tested = 0;
             exchange_out();
         }
         for (uint32_t h = 0; h < acnt; h += 64u) {

@@ -120,3 +120,18 @@ def test_largest_weighted_histograms(kind, los, periodic):
                 assert e.name in ("FCFC_ERANGE", "FCFC_EEDGES"), e
                 refused += 1
     assert taken >= 4 and refused >= 2
+
+
+@pytest.mark.parametrize("ratio", [1.0, 1.5, 9.0, 20.0])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_weight_ranges(ratio, sign):
+    """Weights from all equal to the widest range the exact sums take, of one and of both signs, with
+    zeros, and early merges of the LDS sums."""
+    rng = np.random.default_rng(int(ratio * 10))
+    n = 1500
+    x = synth.uniform_box(n, 60.0, 5)
+    w = np.exp(rng.uniform(0, np.log(ratio), n)) * np.where(rng.random(n) < 0.5, 1.0, sign)
+    w[:3] = 0.0
+    for tune in ({}, {"flush_log2": 8}):
+        check_case("weights", x, kind="smu", edges1=synth.linear_edges(0, 15, 6), edges2=synth.mu_edges(5), los="z",
+                   box=60.0, w1=w, **tune)
