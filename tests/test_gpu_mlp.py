@@ -248,3 +248,34 @@ def test_predict_and_choose_cells():
     assert_same(got.cpu().numpy(), ref, what=f"k={k}")
     c.close()
     plan.close()
+
+
+@pytest.mark.parametrize("m", [1, 15, 17, 65, 16384 + 64 + 5])
+def test_gradient_at_sample_tiles(m):
+    """Sample counts around the 16 samples of a wave, the 64 of a workgroup and
+    one full round of all workgroups, with the tolerance of the gradient test
+    (a 64-term FP32 product per layer and FP32 sums over samples); sums are in a
+    fixed order, so a second call gives the same bits."""
+    import torch
+    from paper_2301_12557_amd import fcfc
+    rng = np.random.default_rng(40 + m)
+    p, nrm = _params(41), _norm()
+    feat = rng.normal(0, 2, (m, 4)).astype(np.float32)
+    tgt = rng.normal(4, 3, m).astype(np.float32)
+    note(f"mlp grad tiles m={m}")
+    md = fcfc.Model(seed=4)
+    md.set(p, nrm)
+    fd, td = torch.from_numpy(feat).cuda(), torch.from_numpy(tgt).cuda()
+    g, loss = md.grad(fd, td)
+    g2, loss2 = md.grad(fd, td)
+    assert np.array_equal(g, g2) and loss == loss2
+    p64, n64, f64 = p.astype(np.float64), nrm.astype(np.float64), feat.astype(np.float64)
+    rl, rg = M.loss_and_grad(p64, n64, f64, tgt.astype(np.float64))
+    assert loss == pytest.approx(rl, rel=1e-4)
+    offs = np.cumsum([0] + [int(np.prod(s)) for _, s in M.SIZES])
+    for (name, _), a, b in zip(M.SIZES, offs[:-1], offs[1:]):
+        scale = np.max(np.abs(rg[a:b]))
+        assert np.max(np.abs(g[a:b].astype(np.float64) - rg[a:b])) <= 1e-3 * scale + 1e-6, name
+    y = md.predict(fd).cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(y - M.predict(p64, n64, f64)) <= 3e-5 * _abs_bound(p64, n64, f64) + 1e-6)
+    md.close()
