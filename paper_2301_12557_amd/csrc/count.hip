@@ -45,9 +45,12 @@ static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 // ---------------------------------------------------------------------------
 // host-side preparation shared by the single and batched drivers
 // ---------------------------------------------------------------------------
+// B points per work item by default, and where the list has to stay short
+constexpr int BCHUNK = 2048, BCHUNK_LONG = 16384;
+
 struct LaunchSetup {
     CountArgs a;  // LDS layout and numeric constants (device pointers bound later)
-    int waves = 16, T = 128, seg = 1, bchunk = 16384, copies = 1;
+    int waves = 16, T = 128, seg = 1, bchunk = BCHUNK, copies = 1;
     std::vector<int4> rows;
     int nrows = 0;
     std::vector<char> htab;  // tables blob: lut1, lut2, band1, band2, E1, E2, stencil rows
@@ -159,9 +162,13 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
     const bool tree = p->tune.tree_leaf > 0 && !batch;
     L.T = (tree || p->tune.tile_points != 64) ? 128 : 64;
     L.seg = tile_seg(p);
-    // B points per item: tree ranges (whole subtrees) are cut finer than the
-    // grid's row pieces, which are short by themselves
-    L.bchunk = p->tune.b_chunk >= 256 ? p->tune.b_chunk : (tree ? 2048 : 16384);
+    // B points per item.  The longest items set the tail of a count whose
+    // points crowd into a few cells (row pieces of a few 10^4 points): on
+    // MI355X 300k points, 90 % of them in ten blobs, ran 13.0 ms at 16384, 8.3
+    // at 4096, 5.9 at 2048, 5.0 at 1024; catalogues without such pieces ran
+    // the same at each.  A batch keeps 16384: its list may not outgrow the
+    // length sized at creation, and its catalogues fill the chip together.
+    L.bchunk = p->tune.b_chunk >= 256 ? p->tune.b_chunk : (batch ? BCHUNK_LONG : BCHUNK);
     L.copies = (p->tune.hist_copies == 2 || p->tune.hist_copies == 4) ? p->tune.hist_copies : 1;
     L.nrows = stencil_rows(p, is_auto, L.rows);
     const bool two = (p->kind == FCFC_BIN_SPERP_PI);
@@ -576,28 +583,37 @@ fcfc_status count_pairs(Plan* p, Cells* c1, Cells* c2, int64_t* d_counts, double
     FCFC_HIP(hipMemcpyAsync(tab, p->host_stage.data(), L.tb_total, hipMemcpyHostToDevice, st));
     int4* srows = bind_tables(L, tab, a);
     fill_u32(ctr, 0u, 64, st);
-    if (tree) {
-        tree_items_enqueue(c1, cb, is_auto, p->rprune, p->coord_max, L.bchunk, nullptr, icount, nullptr, 0, st);
-    } else {
+    if (!tree) {
         hipLaunchKernelGGL(k_tile_count, dim3((unsigned)((nseg + 255) / 256)), dim3(256), 0, st, c1->cell_start, w,
                            tcount);
         scan_exclusive_u32(tcount, toff, nseg, &ctr[0], scan_scr, st);
         hipLaunchKernelGGL(k_tile_write, dim3((unsigned)((nseg + 255) / 256)), dim3(256), 0, st, c1->cell_start,
                            c1->xkey, w, toff, tiles);
-        hipLaunchKernelGGL(k_item_count, dim3((unsigned)((npair_tr + 255) / 256)), dim3(256), 0, st, tiles, &ctr[0],
-                           srows, cb->cell_start, w, icount);
     }
-    scan_exclusive_u32(icount, ioff, npair_tr, &ctr[1], scan_scr, st);
-    uint32_t hctr[2] = {0, 0};
-    FCFC_HIP(hipMemcpyAsync(hctr, ctr, 8, hipMemcpyDeviceToHost, st));
-    FCFC_HIP(hipStreamSynchronize(st));
-    uint32_t nitems = hctr[1];
-    size_t s_items = al256((size_t)std::max<uint32_t>(nitems, 1) * sizeof(Item));
-    size_t s_sort = sorted ? al256((size_t)std::max<uint32_t>(nitems, 1) * 4) : 0;
-    size_t s_rs = sorted ? al256(radix_scratch_bytes(nitems)) : 0;
-    size_t s_times = (p->tune.record_timing && !pr && !ws) ? al256((size_t)std::max<uint32_t>(nitems, 1) * 4) : 0;
-    size_t s_pred = model ? al256((size_t)std::max<uint32_t>(nitems, 1) * 20) : 0;
-    size_t s2 = 2 * s_items + 4 * s_sort + s_rs + s_times + s_pred;
+    // the work list's length, and the scratch it needs
+    uint32_t nitems = 0;
+    size_t s_items = 0, s_sort = 0, s_rs = 0, s_times = 0, s_pred = 0, s2 = 0;
+    for (;;) {
+        if (tree)
+            tree_items_enqueue(c1, cb, is_auto, p->rprune, p->coord_max, L.bchunk, nullptr, icount, nullptr, 0, st);
+        else
+            hipLaunchKernelGGL(k_item_count, dim3((unsigned)((npair_tr + 255) / 256)), dim3(256), 0, st, tiles,
+                               &ctr[0], srows, cb->cell_start, w, icount);
+        scan_exclusive_u32(icount, ioff, npair_tr, &ctr[1], scan_scr, st);
+        uint32_t hctr[2] = {0, 0};
+        FCFC_HIP(hipMemcpyAsync(hctr, ctr, 8, hipMemcpyDeviceToHost, st));
+        FCFC_HIP(hipStreamSynchronize(st));
+        nitems = hctr[1];
+        s_items = al256((size_t)std::max<uint32_t>(nitems, 1) * sizeof(Item));
+        s_sort = sorted ? al256((size_t)std::max<uint32_t>(nitems, 1) * 4) : 0;
+        s_rs = sorted ? al256(radix_scratch_bytes(nitems)) : 0;
+        s_times = (p->tune.record_timing && !pr && !ws) ? al256((size_t)std::max<uint32_t>(nitems, 1) * 4) : 0;
+        s_pred = model ? al256((size_t)std::max<uint32_t>(nitems, 1) * 20) : 0;
+        s2 = 2 * s_items + 4 * s_sort + s_rs + s_times + s_pred;
+        // a list too long for the caller's workspace is cut into longer items
+        if (!ws || s1 + s2 <= ws->bytes || tree || p->tune.b_chunk || L.bchunk == BCHUNK_LONG) break;
+        L.bchunk = w.bchunk = BCHUNK_LONG;
+    }
     char* scr2 = nullptr;
     if (ws) {
         // s1 is a sum of 256-byte multiples, so the second part stays aligned

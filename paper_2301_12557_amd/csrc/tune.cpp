@@ -1,6 +1,6 @@
 // tune.cpp -- the autotuner: picks the tuning knobs of a count (cells per
 // prune radius, histogram copies, tile width, look-up table length,
-// workgroup size, work order) by timing
+// workgroup size, B points per item, work order) by timing
 // real builds and counts on a sample catalogue.  The analytic cell size and
 // its neighbours are always tried; the learned cost model, when given, adds
 // the two cell sizes it predicts fastest; measured GPU time decides.  Knobs never change a count.
@@ -100,12 +100,14 @@ bool cache_lookup(const char* path, const std::string& sig, fcfc_tuning* t, doub
     bool hit = false;
     while (fgets(line, sizeof(line), f)) {
         char s[600];
-        int k, tile, seg, cop, lut, ord, gw;
+        int k, tile, seg, cop, lut, ord, gw, bc = t->b_chunk;
         double m;
-        if (sscanf(line, "%599s %d %d %d %d %d %d %d %lf", s, &k, &tile, &seg, &cop, &lut, &ord, &gw, &m) == 9 &&
+        // (lines written before b_chunk was tuned end at the time)
+        if (sscanf(line, "%599s %d %d %d %d %d %d %d %lf %d", s, &k, &tile, &seg, &cop, &lut, &ord, &gw, &m, &bc) >= 9 &&
             sig == s && k >= 1 && k <= 8 && (tile == 64 || tile == 128) && seg >= 0 && seg <= 64 &&
             (cop == 1 || cop == 2 || cop == 4) && lut >= 10 && lut <= 15 && ord >= 0 && ord <= 2 && gw >= 0 &&
-            gw <= 16 && isfinite(m)) {
+            gw <= 16 && isfinite(m) && (bc == 0 || (bc >= 256 && bc <= (1 << 19)))) {
+            t->b_chunk = bc;
             t->order = ord;
             t->group_waves = gw;
             t->cells_per_rmax = k;
@@ -124,8 +126,8 @@ bool cache_lookup(const char* path, const std::string& sig, fcfc_tuning* t, doub
 void cache_store(const char* path, const std::string& sig, const fcfc_tuning& t, double ms) {
     FILE* f = fopen(path, "a");
     if (!f) return;
-    fprintf(f, "%s %d %d %d %d %d %d %d %.6f\n", sig.c_str(), t.cells_per_rmax, t.tile_points, t.seg_cells,
-            t.hist_copies, t.lut_log2, t.order, t.group_waves, ms);
+    fprintf(f, "%s %d %d %d %d %d %d %d %.6f %d\n", sig.c_str(), t.cells_per_rmax, t.tile_points, t.seg_cells,
+            t.hist_copies, t.lut_log2, t.order, t.group_waves, ms, t.b_chunk);
     fclose(f);
 }
 
@@ -228,8 +230,8 @@ extern "C" fcfc_status fcfc_autotune(fcfc_model_t model, int32_t kind, int32_t l
             bt_free = t;
         }
     }
-    // 2.-6. coordinate descent from a start: histogram copies, tile width,
-    // look-up table length, workgroup size and, with a model, the learned order
+    // 2.-7. coordinate descent from a start: histogram copies, tile width,
+    // B points per item, look-up table length, workgroup size and, with a model, the learned order
     auto descend = [&](const fcfc_tuning& start, double start_ms) {
         bt = start;
         bms = start_ms;
@@ -244,6 +246,15 @@ extern "C" fcfc_status fcfc_autotune(fcfc_model_t model, int32_t kind, int32_t l
             fcfc_tuning t = bt;
             t.tile_points = (bt.tile_points == 64) ? 128 : 64;
             consider(t);
+        }
+        // (a base that sets b_chunk keeps it; shorter items than the default
+        // pay where the points are clustered)
+        if (t0.b_chunk == 0) {
+            for (int bc : {1024, 512}) {
+                fcfc_tuning t = bt;
+                t.b_chunk = bc;
+                consider(t);
+            }
         }
         const int luts[2] = {12, 14};
         for (int lg : luts) {

@@ -109,3 +109,30 @@ def test_noalloc_stats_and_oversized_refusal():
     assert out.cpu().tolist() == [-3] * 4
     cb.close()
     big.close()
+
+
+@pytest.mark.parametrize("n,b_chunk,rc", [(700000, 0, 0), (700000, 2048, -5)])
+def test_noalloc_long_list_is_cut_coarser(n, b_chunk, rc):
+    """All points inside one cell: some 900,000 items of the default length do
+    not fit the scratch array, an eighth of them do, so the default falls back
+    to longer items; a b_chunk the caller set is kept and refused.  The counts
+    are those of the allocating call."""
+    import torch
+    from paper_2301_12557_amd import fcfc
+    lib = fcfc.load()
+    plan = fcfc.Plan("s", synth.linear_edges(0, 100, 4), box=1000.0, cells_per_rmax=1, n_hint=n, b_chunk=b_chunk)
+    x = to_dev(synth.uniform_box(n, 50.0, 9) + 20.0)
+    c = plan.build_cells(x)
+    note(f"noalloc long list b_chunk={b_chunk}")
+    out = torch.full((4,), -3, dtype=torch.int64, device="cuda")
+    assert lib.fcfc_count_pairs_noalloc(plan.h, c.h, None, ctypes.c_void_p(out.data_ptr()), None,
+                                        ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == rc
+    torch.cuda.synchronize()
+    if rc == 0:
+        ref, _ = _counts(lib, "fcfc_count_pairs", plan, c, None, 4, False)
+        assert np.array_equal(out.cpu().numpy(), ref)
+        assert int(ref.sum()) == n * (n - 1) // 2
+    else:
+        assert out.cpu().tolist() == [-3] * 4
+    c.close()
+    plan.close()
