@@ -12,11 +12,12 @@
 //
 // Level by level, the points of each node are ordered along the axis of the
 // longest extent of the node's region (the parent's region cut at the
-// parent's split): one LSD radix sort of a 32-bit key, the node in the high
-// bits and the coordinate on 2^(32 - l) steps across the node's region in the
-// low ones.  The paper
-// splits along the axis of largest variance; the region's extent needs no
-// reduction over the points and gives the same tree on any device.
+// parent's split): one LSD radix sort of a key with the node in the high bits
+// and the coordinate in steps across the node's region in the low ones.  Once
+// a node holds no more than TREE_SUB points, one workgroup orders them through
+// all the levels left, in LDS (k_tree_sub).  The paper splits along the axis of
+// largest variance; the region's extent needs no reduction over the points and
+// gives the same tree on any device.
 #include <math.h>
 #include <string.h>
 
@@ -24,6 +25,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "radix.h"
 #include "worklist.h"
 
 namespace fcfc {
@@ -33,11 +35,8 @@ __device__ inline uint32_t tnode_of_unit(int l, uint64_t u, uint64_t nl) {
     return (uint32_t)((((u + 1) << l) - 1) / nl);
 }
 
-// axis of the longest extent of each node's region at level l (ties: lowest axis)
-__global__ void k_tree_dims(int l, const double* __restrict__ region, int* __restrict__ dims) {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= (1u << l)) return;
-    const double* r = region + 6 * ((size_t)(1u << l) - 1 + k);
+// axis of the longest extent of a region (ties: lowest axis)
+__device__ inline int tree_axis(const double* r) {
     int d = 0;
     double best = r[3] - r[0];
     for (int a = 1; a < 3; a++) {
@@ -47,45 +46,40 @@ __global__ void k_tree_dims(int l, const double* __restrict__ region, int* __res
             d = a;
         }
     }
-    dims[k] = d;
+    return d;
 }
+
+// bits of a level's sort key: the node's l and at least 16 for the coordinate
+// where 32 hold them
+static int tree_key_bits(int l) { return l + 16 <= 24 ? 24 : 32; }
 
 // Sort key of each element at level l: its node (the high l bits; nodes lie
 // in position order, so sorting keeps every node's range) and its coordinate
-// along the node's axis, placed on 2^(32 - l) steps across the node's region
+// along the node's axis, placed on 2^(bits - l) steps across the node's region
 // (the low bits).  Points on one step keep their order; any order of them is
 // a valid split, since every box is formed from the points afterwards.
-__global__ void k_tree_keys(int l, int64_t n, int leaf, uint64_t nl, const double* __restrict__ xyz,
-                            const uint32_t* __restrict__ idx, const int* __restrict__ dims,
-                            const double* __restrict__ region, uint32_t* __restrict__ key,
-                            uint32_t* __restrict__ val) {
+__global__ void k_tree_keys(int l, int bits, int64_t n, int leaf, uint64_t nl, const double* __restrict__ xyz,
+                            const uint32_t* __restrict__ idx, const double* __restrict__ region,
+                            uint32_t* __restrict__ key) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const uint32_t k = tnode_of_unit(l, (uint64_t)i / (uint64_t)leaf, nl);
-    const int d = dims[k];
+    const uint32_t k = tnode_of_unit(l, (uint32_t)i / (uint32_t)leaf, nl);
     const double* r = region + 6 * ((size_t)(1u << l) - 1 + k);
+    const int d = tree_axis(r);
     const double lo = r[d], ext = r[3 + d] - r[d];
     const double x = xyz[3 * (size_t)idx[i] + d];
-    const int b = 32 - l;
+    const int b = bits - l;
     const double steps = ldexp(1.0, b);
     double t = ext > 0.0 ? (x - lo) / ext * steps : 0.0;
     t = fmin(fmax(t, 0.0), steps - 1.0);
     const uint64_t q = (uint64_t)t;
     key[i] = (uint32_t)((b < 32 ? ((uint64_t)k << b) : 0ull) | q);
-    val[i] = (uint32_t)i;
-}
-
-__global__ void k_tree_permute(int64_t n, const uint32_t* __restrict__ val, const uint32_t* __restrict__ in,
-                               uint32_t* __restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = in[val[i]];
 }
 
 // children's regions: the parent's, cut at the coordinate of the first point
 // of the right child along the parent's axis
 __global__ void k_tree_regions(int l, int leaf, uint64_t nl, const double* __restrict__ xyz,
-                               const uint32_t* __restrict__ idx, const int* __restrict__ dims,
-                               double* __restrict__ region) {
+                               const uint32_t* __restrict__ idx, double* __restrict__ region) {
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= (1u << l)) return;
     const size_t h = (size_t)(1u << l) - 1 + k;
@@ -100,10 +94,108 @@ __global__ void k_tree_regions(int l, int leaf, uint64_t nl, const double* __res
     const uint32_t u0 = tunit_bound(l, k, nl), u1 = tunit_bound(l, (uint64_t)k + 1, nl);
     if (u1 - u0 < 2) return;
     const uint32_t m = tunit_bound(l + 1, 2ull * k + 1, nl);
-    const int d = dims[k];
+    const int d = tree_axis(r);
     const double c = xyz[3 * (size_t)idx[(size_t)m * leaf] + d];
     left[3 + d] = c;
     right[d] = c;
+}
+
+// Levels l0 .. L - 1 of the node blockIdx.x of level l0, whose points (TREE_SUB
+// at most, so that they fit the registers and the LDS of one workgroup) are
+// ordered level by level as k_tree_keys and the sort do, with 24-bit keys.  A
+// level in LDS costs 25 us for all nodes together, where keys, three passes
+// of the sort and the regions cost nine launches of 4 to 17 us: on MI355X the
+// trees of 50,021 and 1,000,003 points and their count ran 9.06 -> 6.85 ms,
+// 4.6 of them the count.
+constexpr int TREE_SUB = RS_T * RS_I;
+constexpr int TREE_SUB_UNITS = TREE_SUB / 32;  // leaf units hold 32 points at least
+constexpr int TREE_SUB_BITS = 24;
+
+__global__ __launch_bounds__(RS_T) void k_tree_sub(int l0, int L, int64_t n, int leaf, uint64_t nl,
+                                                   const double* __restrict__ xyz,
+                                                   const double* __restrict__ region, uint32_t* __restrict__ idx) {
+    __shared__ RsShared s;
+    __shared__ uint32_t sk[TREE_SUB], sv[TREE_SUB];
+    __shared__ double reg[2][TREE_SUB_UNITS / 2][6], scale[TREE_SUB_UNITS / 2];
+    __shared__ int axis[TREE_SUB_UNITS / 2];
+    __shared__ uint32_t unode[TREE_SUB_UNITS];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const uint32_t k0 = blockIdx.x;
+    const uint32_t ub0 = tunit_bound(l0, k0, nl), ub1 = tunit_bound(l0, (uint64_t)k0 + 1, nl);
+    const int64_t p0 = (int64_t)ub0 * leaf;
+    const int m = (int)(min<int64_t>((int64_t)ub1 * leaf, n) - p0);
+    if (m <= 0) return;
+    uint32_t key[RS_I], val[RS_I], pos[RS_I], unit[RS_I];
+#pragma unroll
+    for (int r = 0; r < RS_I; r++) {
+        const int e = w * 64 * RS_I + r * 64 + lane;
+        val[r] = e < m ? idx[p0 + e] : 0u;
+        unit[r] = e < m ? (uint32_t)e / (uint32_t)leaf : 0u;
+        key[r] = 0u;
+    }
+    if (t < 6) reg[0][0][t] = region[6 * ((size_t)(1u << l0) - 1 + k0) + t];
+    __syncthreads();
+    for (int l = l0; l < L; l++) {
+        const int sl = l - l0, nsub = 1 << sl, b = TREE_SUB_BITS - sl;
+        const uint32_t kl = k0 << sl;
+        const double(*cur)[6] = reg[sl & 1];
+        double(*nxt)[6] = reg[(sl + 1) & 1];
+        const double steps = ldexp(1.0, b);
+        if (t < nsub) {
+            const int d = tree_axis(cur[t]);
+            const double ext = cur[t][3 + d] - cur[t][d];
+            axis[t] = d;
+            scale[t] = ext > 0.0 ? steps / ext : 0.0;
+        }
+        if (t >= RS_T - TREE_SUB_UNITS) {
+            const uint32_t u = (uint32_t)(t - (RS_T - TREE_SUB_UNITS));
+            if (ub0 + u < ub1) unode[u] = tnode_of_unit(l, ub0 + u, nl) - kl;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < RS_I; r++)
+            if (w * 64 * RS_I + r * 64 + lane < m) {
+                const uint32_t j = unode[unit[r]];
+                const int d = axis[j];
+                const double x = (xyz[3 * (size_t)val[r] + d] - cur[j][d]) * scale[j];
+                key[r] = j << b | (uint32_t)fmin(fmax(x, 0.0), steps - 1.0);
+            }
+        for (int shift = 0; shift < TREE_SUB_BITS; shift += 8) {
+            rs_rank(s, key, shift, m, pos);
+#pragma unroll
+            for (int r = 0; r < RS_I; r++)
+                if (w * 64 * RS_I + r * 64 + lane < m) {
+                    sk[pos[r]] = key[r];
+                    sv[pos[r]] = val[r];
+                }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < RS_I; r++) {
+                const int e = w * 64 * RS_I + r * 64 + lane;
+                if (e < m) {
+                    key[r] = sk[e];
+                    val[r] = sv[e];
+                }
+            }
+        }
+        if (t < nsub && l + 1 < L) {
+            const uint32_t k = kl + (uint32_t)t;
+            for (int a = 0; a < 6; a++) nxt[2 * t][a] = nxt[2 * t + 1][a] = cur[t][a];
+            if (tunit_bound(l, (uint64_t)k + 1, nl) - tunit_bound(l, k, nl) >= 2) {
+                const int d = axis[t];
+                const int64_t at = (int64_t)tunit_bound(l + 1, 2ull * k + 1, nl) * leaf - p0;
+                const double c = xyz[3 * (size_t)sv[at] + d];
+                nxt[2 * t][3 + d] = c;
+                nxt[2 * t + 1][d] = c;
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < RS_I; r++) {
+        const int e = w * 64 * RS_I + r * 64 + lane;
+        if (e < m) idx[p0 + e] = val[r];
+    }
 }
 
 __global__ void k_tree_gather(int64_t n, const double* __restrict__ xyz, const double* __restrict__ w,
@@ -187,15 +279,22 @@ __global__ void k_leaf_local(int64_t n, int leaf, const double* __restrict__ pos
                            (float)(pos64[3 * p + 2] - (double)j.z * q), 0.f);
 }
 
-__global__ void k_box_up(int l, double* __restrict__ box) {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= (1u << l)) return;
-    const size_t h = (size_t)(1u << l) - 1 + k;
-    const double* a = box + 6 * (2 * h + 1);
-    const double* b = box + 6 * (2 * h + 2);
-    for (int i = 0; i < 3; i++) {
-        box[6 * h + i] = fmin(a[i], b[i]);
-        box[6 * h + 3 + i] = fmax(a[3 + i], b[3 + i]);
+// Boxes of the h levels l - 1 .. l - h below which level l is done: a workgroup
+// per node of level l - h takes that node's subtree, level after level.
+constexpr int BOX_UP = 8;
+__global__ __launch_bounds__(256) void k_box_up(int l, int h, double* box) {
+    for (int s = h - 1; s >= 0; s--) {
+        const int lev = l - h + s;
+        for (uint32_t j = threadIdx.x; j < (1u << s); j += 256) {
+            const size_t hp = ((size_t)1 << lev) - 1 + ((size_t)blockIdx.x << s) + j;
+            const double* a = box + 6 * (2 * hp + 1);
+            const double* b = box + 6 * (2 * hp + 2);
+            for (int i = 0; i < 3; i++) {
+                box[6 * hp + i] = fmin(a[i], b[i]);
+                box[6 * hp + 3 + i] = fmax(a[3 + i], b[3 + i]);
+            }
+        }
+        __syncthreads();
     }
 }
 
@@ -255,13 +354,12 @@ fcfc_status build_tree(Plan* p, const fcfc_catalog* cat, hipStream_t st, Cells**
     c->node_box = (double*)(blk + o_box);
     c->tree_q = q;
 
-    // scratch: idx, key, val, tk, tv, idx2, dims, regions, flags + stats, ext slots, sort
+    // scratch: idx, key, tk, tv, regions, flags + stats, ext slots, sort
     const size_t s_n = al256t((size_t)std::max<int64_t>(n, 1) * 4);
-    const size_t s_dims = al256t(((size_t)1 << L) * 4);
     const size_t s_reg = al256t((size_t)nodes * 48);
     const size_t s_misc = 256 + STAT_BYTES;
     const size_t s_sort = al256t(radix_scratch_bytes(n));
-    const size_t stotal = 6 * s_n + s_dims + s_reg + s_misc + STAT_BYTES + s_sort;
+    const size_t stotal = 4 * s_n + s_reg + s_misc + STAT_BYTES + s_sort;
     char* scr = nullptr;
     if (dev_alloc((void**)&scr, stotal, st) != FCFC_OK) {
         dev_free(blk, st);
@@ -271,16 +369,13 @@ fcfc_status build_tree(Plan* p, const fcfc_catalog* cat, hipStream_t st, Cells**
     }
     uint32_t* idx = (uint32_t*)scr;
     uint32_t* key = (uint32_t*)(scr + s_n);
-    uint32_t* val = (uint32_t*)(scr + 2 * s_n);
-    uint32_t* tk = (uint32_t*)(scr + 3 * s_n);
-    uint32_t* tv = (uint32_t*)(scr + 4 * s_n);
-    uint32_t* idx2 = (uint32_t*)(scr + 5 * s_n);
-    int* dims = (int*)(scr + 6 * s_n);
-    double* region = (double*)(scr + 6 * s_n + s_dims);
-    uint32_t* flags = (uint32_t*)(scr + 6 * s_n + s_dims + s_reg);
-    uint64_t* wst = (uint64_t*)(scr + 6 * s_n + s_dims + s_reg + 256);
-    unsigned long long* xslots = (unsigned long long*)(scr + 6 * s_n + s_dims + s_reg + s_misc);
-    void* sort_scr = scr + 6 * s_n + s_dims + s_reg + s_misc + STAT_BYTES;
+    uint32_t* tk = (uint32_t*)(scr + 2 * s_n);
+    uint32_t* tv = (uint32_t*)(scr + 3 * s_n);
+    double* region = (double*)(scr + 4 * s_n);
+    uint32_t* flags = (uint32_t*)(scr + 4 * s_n + s_reg);
+    uint64_t* wst = (uint64_t*)(scr + 4 * s_n + s_reg + 256);
+    unsigned long long* xslots = (unsigned long long*)(scr + 4 * s_n + s_reg + s_misc);
+    void* sort_scr = scr + 4 * s_n + s_reg + s_misc + STAT_BYTES;
     auto fail = [&](fcfc_status s) {
         dev_free(scr, st);
         dev_free(blk, st);
@@ -301,17 +396,19 @@ fcfc_status build_tree(Plan* p, const fcfc_catalog* cat, hipStream_t st, Cells**
         set_error("build_cells: HIP copy failed");
         return fail(FCFC_EHIP);
     }
-    for (int l = 0; l < L; l++) {
-        const unsigned nb = blocks_for((int64_t)1 << l);
-        hipLaunchKernelGGL(k_tree_dims, dim3(nb), dim3(256), 0, st, l, region, dims);
-        hipLaunchKernelGGL(k_tree_keys, dim3(blocks_for(n)), dim3(256), 0, st, l, n, leaf, nl, cat->xyz, idx, dims,
-                           region, key, val);
-        uint32_t *k0 = key, *v0 = val, *k1 = tk, *v1 = tv;
-        radix_sort_pairs(&k0, &v0, &k1, &v1, n, 32, sort_scr, st);
-        hipLaunchKernelGGL(k_tree_permute, dim3(blocks_for(n)), dim3(256), 0, st, n, v0, idx, idx2);
-        std::swap(idx, idx2);
-        hipLaunchKernelGGL(k_tree_regions, dim3(nb), dim3(256), 0, st, l, leaf, nl, cat->xyz, idx, dims, region);
+    // the first level whose nodes fit a workgroup
+    int l0 = 0;
+    while (l0 < L && (int64_t)((nl + ((uint64_t)1 << l0) - 1) >> l0) * leaf > TREE_SUB) l0++;
+    for (int l = 0; l < l0; l++) {
+        const int bits = tree_key_bits(l);
+        hipLaunchKernelGGL(k_tree_keys, dim3(blocks_for(n)), dim3(256), 0, st, l, bits, n, leaf, nl, cat->xyz, idx,
+                           region, key);
+        radix_sort_pairs(&key, &idx, &tk, &tv, n, bits, sort_scr, st);
+        hipLaunchKernelGGL(k_tree_regions, dim3(blocks_for((int64_t)1 << l)), dim3(256), 0, st, l, leaf, nl, cat->xyz,
+                           idx, region);
     }
+    if (l0 < L)
+        hipLaunchKernelGGL(k_tree_sub, dim3(1u << l0), dim3(RS_T), 0, st, l0, L, n, leaf, nl, cat->xyz, region, idx);
     hipLaunchKernelGGL(k_tree_gather, dim3(blocks_for(n)), dim3(256), 0, st, n, cat->xyz, cat->w, idx, c->pos64,
                        c->w, c->abs32);
     hipLaunchKernelGGL(k_box_empty, dim3(blocks_for(nodes)), dim3(256), 0, st, c->node_box, nodes);
@@ -319,8 +416,10 @@ fcfc_status build_tree(Plan* p, const fcfc_catalog* cat, hipStream_t st, Cells**
                        c->node_box, c->leaf_org, xslots);
     hipLaunchKernelGGL(k_leaf_local, dim3(blocks_for(n)), dim3(256), 0, st, n, leaf, c->pos64, c->leaf_org, q,
                        c->pos32);
-    for (int l = L - 1; l >= 0; l--)
-        hipLaunchKernelGGL(k_box_up, dim3(blocks_for((int64_t)1 << l)), dim3(256), 0, st, l, c->node_box);
+    for (int l = L; l > 0; l -= BOX_UP) {
+        const int h = std::min(l, BOX_UP);
+        hipLaunchKernelGGL(k_box_up, dim3(1u << (l - h)), dim3(256), 0, st, l, h, c->node_box);
+    }
     std::vector<uint64_t> hws(STAT_SLOTS * STAT_STRIDE), hx(STAT_SLOTS * STAT_STRIDE);
     uint32_t fl = 0;
     hipError_t e1 = hipMemcpyAsync(&fl, flags, 4, hipMemcpyDeviceToHost, st);
