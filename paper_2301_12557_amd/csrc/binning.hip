@@ -283,8 +283,7 @@ extern "C" fcfc_status fcfc_bin_squared(fcfc_plan_t plan, const double* d_s2, in
             s = FCFC_EHIP;
     }
     if (s == FCFC_OK) {
-        fill_u64((uint64_t*)p->stats_dev, 0ull, 8, st);
-        fill_u64((uint64_t*)d_counts, 0ull, nb, st);
+        zero_ranges(st, {p->stats_dev, 64}, {d_counts, (size_t)nb * 8});
         a.v = d_s2;
         a.n = n;
         a.head = (n > 0 && ((uintptr_t)d_s2 & 15) != 0) ? 1 : 0;

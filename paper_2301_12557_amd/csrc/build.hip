@@ -59,6 +59,29 @@ void fill_u64(uint64_t* p, uint64_t v, int64_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(n)), dim3(256), 0, st, p, v, n);
 }
 
+struct ZeroArgs {
+    uint32_t* p[4];
+    int64_t end[4];  // running sum of the words
+};
+__global__ void k_zero(ZeroArgs z) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < z.end[3];
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int r = i < z.end[0] ? 0 : i < z.end[1] ? 1 : i < z.end[2] ? 2 : 3;
+        z.p[r][i - (r ? z.end[r - 1] : 0)] = 0u;
+    }
+}
+void zero_ranges(hipStream_t st, ZeroRange a, ZeroRange b, ZeroRange c, ZeroRange d) {
+    const ZeroRange r[4] = {a, b, c, d};
+    ZeroArgs z;
+    int64_t n = 0;
+    for (int i = 0; i < 4; i++) {
+        z.p[i] = (uint32_t*)r[i].p;
+        n += (int64_t)(r[i].bytes / 4);
+        z.end[i] = n;
+    }
+    if (n > 0) hipLaunchKernelGGL(k_zero, dim3(grid_for(n, 256, 1024)), dim3(256), 0, st, z);
+}
+
 int device_cu_count() {
     int dev = 0, cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 256;
@@ -516,10 +539,12 @@ __global__ __launch_bounds__(256) void k_gather(const double* __restrict__ xyz, 
                                                 const uint32_t* __restrict__ skey,
                                                 const uint32_t* __restrict__ sidx, int64_t n, GridArgs g, int xbits,
                                                 float4* __restrict__ pos32, float4* __restrict__ abs32,
-                                                double* __restrict__ pos64, double* __restrict__ wout) {
+                                                double* __restrict__ pos64, double* __restrict__ wout,
+                                                uint32_t* __restrict__ xkey) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     uint32_t i = sidx[p];
+    xkey[p] = skey[p];
     uint32_t key = skey[p] >> xbits;
     uint32_t cx = key % (uint32_t)g.nx;
     uint32_t cy = (key / (uint32_t)g.nx) % (uint32_t)g.ny;
@@ -648,10 +673,8 @@ fcfc_status build_cells(Plan* p, const fcfc_catalog* cat, hipStream_t st, Cells*
     void* sort_scr = scr + 4 * s_keys + s_misc;
 
     GridArgs g = make_grid_args(p);
-    fill_u32((uint32_t*)(c->pos32 + n), 0u, PAD * 4, st);
-    if (weighted) fill_u64((uint64_t*)(c->w + n), 0ull, PAD, st);
-    fill_u32(flags, 0u, 1, st);
-    fill_u64(wst, 0ull, STAT_SLOTS * STAT_STRIDE, st);
+    zero_ranges(st, {c->pos32 + n, (size_t)PAD * 16}, {weighted ? c->w + n : nullptr, weighted ? (size_t)PAD * 8 : 0},
+                {flags, s_misc});
     if (n > 0) {
         hipLaunchKernelGGL(k_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, cat->xyz, cat->w, n, g,
                            c->xbits, key, idx, flags, wst);
@@ -660,30 +683,23 @@ fcfc_status build_cells(Plan* p, const fcfc_catalog* cat, hipStream_t st, Cells*
         bits = std::min(32, bits + c->xbits);
         radix_sort_pairs(&key, &idx, &tk, &tv, n, bits, sort_scr, st);
         hipLaunchKernelGGL(k_gather, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, cat->xyz, cat->w, key,
-                           idx, n, g, c->xbits, c->pos32, c->abs32, c->pos64, c->w);
-        if (hipMemcpyAsync(c->xkey, key, (size_t)n * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) {
-            dev_free(scr, st);
-            dev_free(blk, st);
-            delete c;
-            set_error("build_cells: HIP copy failed");
-            return FCFC_EHIP;
-        }
+                           idx, n, g, c->xbits, c->pos32, c->abs32, c->pos64, c->w, c->xkey);
     }
     hipLaunchKernelGGL(k_cell_start, dim3((unsigned)((ncell + 1 + 255) / 256)), dim3(256), 0, st, key, n, ncell,
                        c->xbits, c->cell_start);
     uint64_t h[3] = {0, 0, 0};
-    std::vector<uint64_t> hws(STAT_SLOTS * STAT_STRIDE);
-    hipError_t e1 = hipMemcpyAsync(h, flags, 8, hipMemcpyDeviceToHost, st);
-    hipError_t e2 = hipMemcpyAsync(hws.data(), wst, STAT_BYTES, hipMemcpyDeviceToHost, st);
+    // flags and, of a weighted set, the weight range behind them, in one copy
+    std::vector<uint64_t> hmisc((weighted ? s_misc : 256) / 8);
+    hipError_t e1 = hipMemcpyAsync(hmisc.data(), flags, hmisc.size() * 8, hipMemcpyDeviceToHost, st);
     hipError_t e3 = hipStreamSynchronize(st);
     dev_free(scr, st);
-    if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) {
+    if (e1 != hipSuccess || e3 != hipSuccess) {
         dev_free(blk, st);
         delete c;
-        set_error("build_cells: HIP error %s", hipGetErrorString(e3 != hipSuccess ? e3 : (e2 != hipSuccess ? e2 : e1)));
+        set_error("build_cells: HIP error %s", hipGetErrorString(e3 != hipSuccess ? e3 : e1));
         return FCFC_EHIP;
     }
-    uint32_t fl = (uint32_t)h[0];
+    uint32_t fl = (uint32_t)hmisc[0];
     fcfc_status s = FCFC_OK;
     if (fl & (VF_NONFINITE | VF_WNONFINITE)) {
         set_error("build_cells: non-finite position or weight");
@@ -698,7 +714,7 @@ fcfc_status build_cells(Plan* p, const fcfc_catalog* cat, hipStream_t st, Cells*
         return s;
     }
     if (weighted) {
-        weight_stats_reduce(hws.data(), &h[1], &h[2]);
+        weight_stats_reduce(hmisc.data() + 256 / 8, &h[1], &h[2]);
         double a, b;
         memcpy(&a, &h[1], 8);
         memcpy(&b, &h[2], 8);

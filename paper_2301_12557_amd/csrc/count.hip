@@ -668,7 +668,8 @@ fcfc_status count_pairs(Plan* p, Cells* c1, Cells* c2, int64_t* d_counts, double
         FCFC_HIP(hipEventCreate(&p->ev1));
     }
     const bool keep_stats = p->stats_dev != nullptr;
-    if (keep_stats) fill_u64((uint64_t*)p->stats_dev, 0ull, 8, st);
+    zero_ranges(st, {p->stats_dev, keep_stats ? (size_t)64 : 0}, {d_counts, (size_t)p->nbins * 8},
+                {wacc, weighted ? (size_t)p->nbins * 16 : 0});
     if (sorted && nitems > 1) {
         uint32_t* k0 = (uint32_t*)(scr2 + 2 * s_items);
         uint32_t* v0 = (uint32_t*)(scr2 + 2 * s_items + s_sort);
@@ -695,9 +696,6 @@ fcfc_status count_pairs(Plan* p, Cells* c1, Cells* c2, int64_t* d_counts, double
         run_items = items2;
     }
     uint32_t* times = p->tune.record_timing ? (uint32_t*)(scr2 + 2 * s_items + 4 * s_sort + s_rs) : nullptr;
-
-    fill_u64((uint64_t*)d_counts, 0ull, p->nbins, st);
-    if (weighted) fill_u64((uint64_t*)wacc, 0ull, 2 * (int64_t)p->nbins, st);
 
     a.posA = c1->pos32;
     a.absA = c1->abs32;
@@ -918,9 +916,8 @@ static void batch_enqueue_back(BatchImpl* b, hipStream_t st) {
     }
     hipLaunchKernelGGL(k_chunk_prefix, dim3(1), dim3(1), 0, st, b->pair_items, b->pair_order, b->npairs,
                        b->L.a.chunk_items, b->chunk_prefix, &b->ctr[3]);
-    fill_u64((uint64_t*)b->counts, 0ull, (int64_t)b->npairs * p->nbins, st);
-    if (b->weighted) fill_u64((uint64_t*)b->wacc, 0ull, 2 * (int64_t)b->npairs * p->nbins, st);
-    fill_u64((uint64_t*)b->kstats, 0ull, 8, st);
+    zero_ranges(st, {b->counts, (size_t)b->npairs * p->nbins * 8},
+                {b->wacc, b->weighted ? (size_t)b->npairs * p->nbins * 16 : 0}, {b->kstats, 64});
     hipLaunchKernelGGL(b->L.kern, dim3((unsigned)b->nblk), dim3(b->L.waves * 64), (size_t)b->L.a.lds_bytes, st,
                        (const CountArgs*)b->args_dev);
     if (b->weighted)

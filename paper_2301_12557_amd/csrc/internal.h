@@ -223,6 +223,13 @@ fcfc_status validate_points(Plan* p, const fcfc_catalog* cat, uint32_t* idx, uin
 fcfc_status fit_bounds(Plan* p, const fcfc_catalog* cats, int ncat, hipStream_t st);
 void fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t st);
 void fill_u64(uint64_t* p, uint64_t v, int64_t n, hipStream_t st);
+// Clears up to four buffers (of whole 32-bit words) in one launch.
+struct ZeroRange {
+    void* p;
+    size_t bytes;
+};
+void zero_ranges(hipStream_t st, ZeroRange a, ZeroRange b = {nullptr, 0}, ZeroRange c = {nullptr, 0},
+                 ZeroRange d = {nullptr, 0});
 // relative error bound assumed for the hardware FP32 rsq and rcp (plan.cpp)
 double trans_rel_bound();
 

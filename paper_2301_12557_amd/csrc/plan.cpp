@@ -200,25 +200,21 @@ static fcfc_status build_lut(Lut1D& t, const std::vector<double>& edges, const E
     t.scale = (float)scale;
     int64_t nt = (int64_t)ceil((double)t.vmax * scale) + 1;
     if (nt > 32767) nt = 32767;  // cannot happen with log2_target <= 14
+    // Entry j covers [j, j + 1) / scale (exact: the scale is a power of two).
+    // Entries free of bands hold the number of band ends at or below them;
+    // the entries that meet a band hold its code, the first band's where
+    // several meet one entry (written last).  Runs are filled whole: a test of
+    // every edge for every entry took half of a small count (20,000 points in
+    // 20 bins: plan 0.46 -> 0.01 ms).
     t.tab.assign((size_t)nt, LUT_NONE);
-    for (int64_t j = 0; j < nt; j++) {
-        double a = (double)j / scale, b = (double)(j + 1) / scale;  // entry [a, b)
-        int klo = -1;
-        for (int k = 0; k <= t.n; k++) {
-            if (t.hi[k] <= t.lo[k]) continue;  // empty band
-            if ((double)t.lo[k] < b && (double)t.hi[k] > a) {
-                klo = k;
-                break;
-            }
-        }
-        if (klo >= 0) {
-            t.tab[j] = lut_hot_code(klo);
-        } else {
-            int c = 0;
-            for (int k = 0; k <= t.n; k++)
-                if ((double)t.hi[k] <= a) c = k + 1;
-            t.tab[j] = (c >= 1 && c <= t.n) ? (int16_t)(c - 1) : (int16_t)LUT_NONE;
-        }
+    auto entry = [&](double x) { return (int64_t)std::min(std::max(x, 0.0), (double)nt); };
+    for (int k = 0; k < t.n; k++)
+        std::fill(t.tab.begin() + entry(ceil((double)t.hi[k] * scale)),
+                  t.tab.begin() + entry(ceil((double)t.hi[k + 1] * scale)), (int16_t)k);
+    for (int k = t.n; k >= 0; k--) {
+        if (t.hi[k] <= t.lo[k]) continue;  // empty band
+        std::fill(t.tab.begin() + entry(floor((double)t.lo[k] * scale)),
+                  t.tab.begin() + entry(ceil((double)t.hi[k] * scale)), lut_hot_code(k));
     }
     return FCFC_OK;
 }

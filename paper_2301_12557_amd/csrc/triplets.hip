@@ -815,10 +815,8 @@ extern "C" fcfc_status fcfc_count_triplets(fcfc_plan_t plan, fcfc_cells_t cells,
             s = FCFC_EHIP;
     }
     if (s == FCFC_OK) {
-        fill_u64((uint64_t*)(blk + o_out), 0ull, a.nhist, st);
-        if (weighted) fill_u64((uint64_t*)(blk + o_w), 0ull, 2 * (int64_t)a.nhist, st);
-        fill_u32((uint32_t*)(blk + o_cur), 0u, 1, st);
-        fill_u64((uint64_t*)p->stats_dev, 0ull, 8, st);
+        zero_ranges(st, {blk + o_out, (size_t)a.nhist * 8}, {blk + o_w, weighted ? (size_t)a.nhist * 16 : 0},
+                    {blk + o_cur, 4}, {p->stats_dev, 64});
         a.pos = c->pos64;
         a.w = weighted ? c->w : nullptr;
         a.wscale = ldexp(1.0, S);
