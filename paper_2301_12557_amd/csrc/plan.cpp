@@ -235,22 +235,27 @@ fcfc_status plan_bin_table(Plan* p, const Lut1D** out) {
     return FCFC_OK;
 }
 
-fcfc_status plan_side_table(Plan* p, double e_axis, const Lut1D** out) {
-    if (p->luttri.n == 0 || p->luttri_e != e_axis) {
+fcfc_status plan_side_tables(Plan* p, double e_axis, double e_abs, int lg, const Lut1D** wide, const Lut1D** narrow) {
+    if (p->luttri.n == 0 || p->luttri_e != e_axis || p->luttri_lg != lg) {
         // |Q32 - Q64| <= 2 sqrt3 e sqrt(Q) + 3 e^2 + 3.3 u Q for a squared
         // length formed by an fma chain from FP32 components each within e of
-        // the FP64 ones (the same form as the pair counts' squared separation)
+        // the FP64 ones (the same form as the pair counts' squared separation);
+        // one formed by a matrix product is off by up to e_abs more
         ErrModel m;
         m.A = 2.0 * sqrt(3.0) * e_axis;
         m.B = 3.0 * e_axis * e_axis;
         m.C = 3.3 * U32 + 1e-15;
-        const int lg = p->tune.lut_log2 > 0 ? std::min(14, std::max(8, p->tune.lut_log2)) : 13;
-        Lut1D t;
+        Lut1D t, tn;
+        FCFC_TRY(build_lut(tn, p->e1, m, 8));  // (its bands only)
+        m.B += e_abs;
         FCFC_TRY(build_lut(t, p->e1, m, lg));
         p->luttri = t;
+        p->luttri_n = tn;
         p->luttri_e = e_axis;
+        p->luttri_lg = lg;
     }
-    *out = &p->luttri;
+    *wide = &p->luttri;
+    *narrow = &p->luttri_n;
     return FCFC_OK;
 }
 

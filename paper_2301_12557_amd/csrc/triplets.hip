@@ -13,11 +13,18 @@
 // Lists longer than the LDS region are taken in chunks: chunk A against itself
 // and against every later chunk B, each chunk rebuilt by rescanning the cells.
 //
-// Sides are formed in FP32 from displacements relative to the primary and
-// binned with a banded look-up table (binlut.h) whose bands cover the FP32
-// error; a side inside an edge's band is formed again in FP64, in the same
-// operation order as the pair definition, and binned exactly, so the counts
-// equal those of the FP64 definition.
+// Sides are formed in FP32 from displacements relative to the primary, 256 at a
+// time on the matrix cores, and binned with a banded look-up table (binlut.h)
+// whose bands cover the FP32 error; a side inside an edge's band is formed
+// again in FP64, in the same operation order as the pair definition, and
+// binned exactly, so the counts equal those of the FP64 definition.
+//
+// Bound by vector issue: about 46 instructions for each block of 16 x 16 sides
+// (a block's four look-ups and counts per lane; the sides themselves are one
+// matrix instruction) and as many again per primary to scan the cells around
+// it, where nine of ten points fail the distance.  MI355X, 1,000,003 points,
+// 15 bins to 30 (57 neighbours after a primary): kernel 3.39 -> 2.57 ms.
+// (Reading a step ahead while scanning, or a block ahead, does not pay: 2.8.)
 //
 // Weighted counts: a triangle weighs fl(fl(a b) c) for its three point
 // weights sorted by value, a <= b <= c (independent of the point order); a
@@ -30,6 +37,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 #include <vector>
 
 #include "binlut.h"
@@ -38,9 +46,6 @@
 namespace fcfc {
 
 constexpr int TRI_CAP = 128;       // list entries per LDS region (two regions per wave)
-// pairs of a list taken by column q in groups (p, q), (p + 1, q), p even; a
-// full list has TRI_CAP^2 / 4 groups
-constexpr int TRI_GROUPS = TRI_CAP / 2 * ((TRI_CAP + 1) / 2);
 constexpr int TRI_ORDERED_MAX_BINS = 16;  // ordered counters (nb^3 of them) up to this many bins
 constexpr int TRI_MAX_WAVES = 16;
 constexpr int TRI_MAX_BINS = 32;   // sorted bin triples: C(34, 3) = 5984 u64 counters
@@ -63,10 +68,9 @@ struct TriArgs {
     int off_wl;               // LDS: three u64 limbs per counter
     const uint4* tab;         // table blob for FP32 squared sides (binlut.h layout)
     int tab_words;
-    int off_band, off_e, off_hist, off_t3, off_ptab, off_lists;
-    int lists_words;          // 16-byte words of the list regions
+    int off_band, off_e, off_nband, off_hist, off_t3, off_lists;
     int nb;
-    float scale, vmax;
+    float scale, vmax, inv_scale;
     float top;                // index of the table's last entry (out of range), as a float
     int nhist;                // counters: sorted bin triples, or nb^3 ordered ones
     unsigned long long* out;  // nhist counters (accumulated)
@@ -89,21 +93,24 @@ __device__ __attribute__((always_inline)) inline double side2(double ax, double 
     return (dx * dx + dy * dy) + dz * dz;  // built with -ffp-contract=off
 }
 
-// Bin of a squared side v >= 0 formed in FP32 (table bands cover its error):
-// the bin, -1 (out of range) or -2 (inside an edge's band: the FP64 side
-// decides).  The index is clamped to the table's last entry, which lies above
-// the top band and holds "out of range".
-__device__ __attribute__((always_inline)) inline int bin32(const BinTable& T, float top, float v) {
-    int e = T.lut[(uint32_t)fminf(v * T.scale, top)];
-    if (e < -1) {
-        const int k0 = -2 - e;
-        e = bin_near(T, k0, v);
-        if (e == -2)
-            e = bin_hot(T.band, T.nb, k0, v);
-        else if (e >= T.nb)
-            e = -1;
-    }
-    return e;
+// Table entry of a squared side times the table's scale: the bin, -1 (out of
+// range) or a band's code (<= -2).  The index is clamped to the table, whose
+// last entry lies above the top band and holds "out of range".
+__device__ __attribute__((always_inline)) inline int tri_entry(const BinTable& T, float top, float vs) {
+    return T.lut[(uint32_t)__builtin_amdgcn_fmed3f(vs, 0.0f, top)];
+}
+
+// Bin of a squared side v whose table entry e is a band's code: from the
+// table's bands, which cover the error of the matrix product; inside one of
+// them from `near`, the square of the FP32 difference, and the narrower bands
+// of its error.  -2: inside one of those too, the FP64 side decides.
+template <typename F>
+__device__ __attribute__((always_inline)) inline int tri_hot(const BinTable& T, const float2* nband, int e, float v,
+                                                            F near) {
+    const int k0 = -2 - e;
+    e = bin_near(T, k0, v);
+    if (e == -2) return bin_hot(nband, T.nb, k0, near());
+    return e >= T.nb ? -1 : e;
 }
 
 // Counter of the sorted bin triple a <= b <= c: C(c+2, 3) + C(b+1, 2) + a,
@@ -116,24 +123,18 @@ __device__ __attribute__((always_inline)) inline int tri_slot(const int* t3, int
     return t3[hi] + (int)(__umul24((uint32_t)mid, (uint32_t)mid + 1u) >> 1) + lo;
 }
 
-// Counter of the ordered bin triple (b1, b2, b3): (b1 nb + b2) nb + b3.  A list
-// entry of bin b holds the code b nb^2 | (b nb) << 16, so the counter of the
-// triangle (primary, p, q) with third side in bin s is
-// (code_p & 0xffff) + (code_q >> 16) + s.  The six orders of a triple are
-// summed into its sorted bin after the count.
-__device__ __attribute__((always_inline)) inline uint32_t tri_code(uint32_t bin, uint32_t nb) {
-    const uint32_t c1 = __umul24(bin, nb);
-    return __umul24(c1, nb) | (c1 << 16);
-}
+// Counter of the ordered bin triple (b1, b2, b3): (b1 nb + b2) nb + b3, the
+// side bins of (primary, p), (primary, q) and (p, q).  The six orders of a
+// triple are summed into its sorted bin after the count.
 
 // A list of neighbours of the primary: each entry's displacement from the
-// primary in FP32 with the bin of its side to the primary, or that bin's code
-// for ordered counters (bits of .w), its sorted index and, for weighted
-// counts, its weight.
+// primary in FP32 with its square, its sorted index, the bin of its side to the
+// primary and, for weighted counts, its weight.
 struct TriList {
     float4* d;
-    uint32_t* idx;
     double* w;
+    uint32_t* idx;
+    uint8_t* bin;
 };
 
 // weight of a triangle: the three weights sorted by value, fl(fl(a b) c)
@@ -161,35 +162,82 @@ __device__ inline uint32_t lane_prefix_tri(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// One candidate neighbour j of the primary: the FP64 displacement of the
-// definition (minimum image when Lw > 0), rounded to FP32, with the bin of its
-// squared length (from the FP32 square; inside an edge's band from the FP64
-// one) or -1.
-template <bool U>
-__device__ __attribute__((always_inline)) inline int tri_point(const TriArgs& a, const BinTable& T, double dx,
-                                                              double dy, double dz, double Lw, float4& e,
-                                                              uint32_t& rechk) {
+// The ranges of sorted points around a cell: lane l holds range l & 1 of
+// stencil row s0 + l / 2 (a periodic run of cells wraps once at most).  `mix`:
+// ranges in the cell's own z.
+struct TriRanges {
+    uint32_t b0, cnt, excl, total;
+    uint64_t open, mix;
+};
+
+__device__ inline void tri_ranges(const TriArgs& a, int s0, int cx, int cy, int cz, int lane, TriRanges& r) {
+    uint32_t b0 = 0, b1 = 0;
+    bool mixed = false;
+    const int s = s0 + (lane >> 1);
+    if (s < a.nst) {
+        const int4 o = a.stencil[s];
+        int y = cy + o.x, z = cz + o.y, xa = cx + o.z, xb = cx + o.w;
+        int pa1 = 1, pb1 = 0;
+        bool inside_grid = true;
+        if (a.L > 0.0) {
+            y += y < 0 ? a.ny : (y >= a.ny ? -a.ny : 0);
+            z += z < 0 ? a.nz : (z >= a.nz ? -a.nz : 0);
+            if (xa < 0) {
+                pa1 = 0;
+                pb1 = xb;
+                xa += a.nx;
+                xb = a.nx - 1;
+            } else if (xb >= a.nx) {
+                pa1 = 0;
+                pb1 = xb - a.nx;
+                xb = a.nx - 1;
+            }
+        } else {
+            inside_grid = y >= 0 && y < a.ny && z >= 0 && z < a.nz;
+            xa = max(xa, 0);
+            xb = min(xb, a.nx - 1);
+        }
+        const int x0 = (lane & 1) ? pa1 : xa, x1 = (lane & 1) ? pb1 : xb;
+        if (inside_grid && x0 <= x1 && z >= cz) {
+            const uint32_t row = ((uint32_t)z * (uint32_t)a.ny + (uint32_t)y) * (uint32_t)a.nx;
+            b0 = a.cs[row + (uint32_t)x0];
+            b1 = a.cs[row + (uint32_t)x1 + 1u];
+            mixed = z == cz;
+        }
+    }
+    const uint32_t cnt = b1 - b0;
+    // inclusive sum over the wave: within rows of 16 lanes, then across the rows
+    int incl = (int)cnt;
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, false);  // row_shr:1
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, false);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, false);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, false);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    r.b0 = b0;
+    r.cnt = cnt;
+    r.excl = (uint32_t)incl - cnt;
+    r.total = (uint32_t)__builtin_amdgcn_readlane(incl, 63);
+    r.open = __ballot(cnt > 0);
+    r.mix = __ballot(mixed);
+}
+
+// The FP64 displacement of the definition (minimum image when Lw > 0).
+__device__ __attribute__((always_inline)) inline void tri_wrap(double& dx, double& dy, double& dz, double Lw,
+                                                              double h) {
     if (Lw > 0.0) {
-        const double h = a.halfL;
         dx = dx > h ? dx - Lw : (dx < -h ? dx + Lw : dx);
         dy = dy > h ? dy - Lw : (dy < -h ? dy + Lw : dy);
         dz = dz > h ? dz - Lw : (dz < -h ? dz + Lw : dz);
     }
-    e = make_float4((float)dx, (float)dy, (float)dz, 0.f);
-    int bin = bin32(T, a.top, __builtin_fmaf(e.z, e.z, __builtin_fmaf(e.y, e.y, e.x * e.x)));
-    if (bin == -2) {
-        rechk++;
-        bin = bin_exact(T.E, T.nb, (dx * dx + dy * dy) + dz * dz);
-    }
-    e.w = __uint_as_float(U ? tri_code((uint32_t)bin, (uint32_t)a.nb) : (uint32_t)bin);
-    return bin;
 }
 
 // Scan the cells around primary i (cell cx, cy, cz) and keep the neighbours
-// after i with side ij in range whose position in the scan order lies in
+// after i below the top edge's band whose position in the scan order lies in
 // [lo, lo + TRI_CAP), into R.  Returns the number found up to the point the
 // scan stopped (all of them when `whole`).  nside (wave-uniform) counts the
-// points scanned.
+// points scanned.  `rg` holds the ranges of the cell when the stencil has no
+// more than 32 rows.
 //
 // "After" is the order of the stored coordinates (z, then y, then x, then the
 // sorted index): a triangle is found once, from its first vertex in that
@@ -201,122 +249,68 @@ __device__ __attribute__((always_inline)) inline int tri_point(const TriArgs& a,
 // i's own z cell are tested point by point.
 //
 // The scan order is the stencil's rows in turn, each row's one or two index
-// ranges (a periodic run of cells wraps once at most), and the points of a
-// range by index.  The ranges of up to 32 rows are fetched at once, one per
-// lane, and their concatenation is then taken 128 positions at a time, two
-// per lane, so that the loads of a step do not wait on one another.
-template <bool W, bool U>
-__device__ uint32_t tri_gather(const TriArgs& a, const BinTable& T, int64_t i, double xi, double yi, double zi,
-                               uint32_t icell, int cx, int cy, int cz, double Lw, uint32_t lo, bool whole,
-                               const TriList& R, int lane, unsigned long long& nside, uint32_t& rechk) {
+// ranges, and the points of a range by index.  The ranges' concatenation is
+// taken 128 positions at a time, two per lane, so that the loads of a step do
+// not wait on one another.  Only the distance is tested here: nine of ten
+// points scanned fail it (tri_bins looks up the bins of those kept).
+__device__ inline uint32_t tri_gather(const TriArgs& a, float vmax, int64_t i, double xi, double yi, double zi, int cx,
+                                      int cy, int cz, double Lw, uint32_t lo, bool whole, const TriRanges& rg,
+                                      const TriList& R, int lane, unsigned long long& nside) {
     uint32_t running = 0;
     const uint32_t hi = lo + TRI_CAP;
     for (int s0 = 0; s0 < a.nst; s0 += 32) {
-        // lane l: range (l & 1) of row s0 + l / 2; mixed: a row of i's z cell
-        uint32_t b0 = 0, b1 = 0;
-        bool mixed = false;
-        const int s = s0 + (lane >> 1);
-        if (s < a.nst) {
-            const int4 o = a.stencil[s];
-            int y = cy + o.x, z = cz + o.y, xa = cx + o.z, xb = cx + o.w;
-            int pa1 = 1, pb1 = 0;
-            bool inside_grid = true;
-            if (a.L > 0.0) {
-                y += y < 0 ? a.ny : (y >= a.ny ? -a.ny : 0);
-                z += z < 0 ? a.nz : (z >= a.nz ? -a.nz : 0);
-                if (xa < 0) {
-                    pa1 = 0;
-                    pb1 = xb;
-                    xa += a.nx;
-                    xb = a.nx - 1;
-                } else if (xb >= a.nx) {
-                    pa1 = 0;
-                    pb1 = xb - a.nx;
-                    xb = a.nx - 1;
-                }
-            } else {
-                inside_grid = y >= 0 && y < a.ny && z >= 0 && z < a.nz;
-                xa = max(xa, 0);
-                xb = min(xb, a.nx - 1);
-            }
-            const int x0 = (lane & 1) ? pa1 : xa, x1 = (lane & 1) ? pb1 : xb;
-            if (inside_grid && x0 <= x1 && z >= cz) {
-                const uint32_t row = ((uint32_t)z * (uint32_t)a.ny + (uint32_t)y) * (uint32_t)a.nx;
-                b0 = a.cs[row + (uint32_t)x0];
-                b1 = a.cs[row + (uint32_t)x1 + 1u];
-                mixed = z == cz;
-            }
-        }
-        const uint32_t cnt = b1 - b0;
-        uint32_t incl = cnt;
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t v = (uint32_t)__shfl_up((int)incl, d, 64);
-            if (lane >= d) incl += v;
-        }
-        const uint32_t excl = incl - cnt;
-        const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        // ranges not yet used up, in scan order (wave-uniform); ranges of i's z cell
-        uint64_t open = __ballot(cnt > 0);
-        const uint64_t mixm = __ballot(mixed);
+        TriRanges r = rg;
+        if (a.nst > 32) tri_ranges(a, s0, cx, cy, cz, lane, r);
+        // ranges not yet used up, in scan order (wave-uniform)
+        uint64_t open = r.open;
         bool stop = false;
-        for (uint32_t c0 = 0; c0 < total && !stop; c0 += 128) {
+        for (uint32_t c0 = 0; c0 < r.total && !stop; c0 += 128) {
             const uint32_t g0 = c0 + (uint32_t)lane, g1 = g0 + 64u;
             uint32_t j0 = 0, j1 = 0;
-            bool t0 = false, t1 = false;  // the point lies in i's z cell: test its order
+            uint64_t t0 = 0, t1 = 0;  // lanes whose point lies in i's z cell: test its order
             while (open) {
                 const int L = __builtin_ctzll(open);
-                const uint32_t se = (uint32_t)__builtin_amdgcn_readlane((int)excl, L);
-                const uint32_t sc = (uint32_t)__builtin_amdgcn_readlane((int)cnt, L);
-                const uint32_t sb = (uint32_t)__builtin_amdgcn_readlane((int)b0, L);
-                const bool mx = (mixm >> L) & 1ull;
+                const uint32_t se = (uint32_t)__builtin_amdgcn_readlane((int)r.excl, L);
+                const uint32_t sc = (uint32_t)__builtin_amdgcn_readlane((int)r.cnt, L);
+                const uint32_t sb = (uint32_t)__builtin_amdgcn_readlane((int)r.b0, L);
                 if (se >= c0 + 128u) break;
-                if (g0 - se < sc) {
-                    j0 = sb + (g0 - se);
-                    t0 = mx;
-                }
-                if (g1 - se < sc) {
-                    j1 = sb + (g1 - se);
-                    t1 = mx;
+                const uint64_t m0 = __ballot(g0 - se < sc), m1 = __ballot(g1 - se < sc);
+                j0 = g0 - se < sc ? sb + (g0 - se) : j0;
+                j1 = g1 - se < sc ? sb + (g1 - se) : j1;
+                if ((r.mix >> L) & 1ull) {
+                    t0 |= m0;
+                    t1 |= m1;
                 }
                 if (se + sc > c0 + 128u) break;  // the range goes on into the next step
                 open &= open - 1;
             }
-            const bool v0 = g0 < total, v1 = g1 < total;
-            double p0x = 0, p0y = 0, p0z = 0, p1x = 0, p1y = 0, p1z = 0;
-            if (v0) {
-                p0x = a.pos[3 * (size_t)j0];
-                p0y = a.pos[3 * (size_t)j0 + 1];
-                p0z = a.pos[3 * (size_t)j0 + 2];
-            }
-            if (v1) {
-                p1x = a.pos[3 * (size_t)j1];
-                p1y = a.pos[3 * (size_t)j1 + 1];
-                p1z = a.pos[3 * (size_t)j1 + 2];
-            }
+            const bool v0 = g0 < r.total, v1 = g1 < r.total;
+            // (a lane past the end reads point 0 and drops it)
+            const double p0x = a.pos[3 * (size_t)j0], p0y = a.pos[3 * (size_t)j0 + 1], p0z = a.pos[3 * (size_t)j0 + 2];
+            const double p1x = a.pos[3 * (size_t)j1], p1y = a.pos[3 * (size_t)j1 + 1], p1z = a.pos[3 * (size_t)j1 + 2];
 #pragma unroll
             for (int h = 0; h < 2; h++) {
                 const uint32_t j = h ? j1 : j0;
                 const double px = h ? p1x : p0x, py = h ? p1y : p0y, pz = h ? p1z : p0z;
-                const bool after = !(h ? t1 : t0) ||
-                                   (pz > zi || (pz == zi && (py > yi || (py == yi && (px > xi || (px == xi && j > i))))));
-                const bool v = (h ? v1 : v0) && after;
-                float4 e = make_float4(0.f, 0.f, 0.f, 0.f);
-                int bin = -1;
-                if (v) bin = tri_point<U>(a, T, px - xi, py - yi, pz - zi, Lw, e, rechk);
-                const bool ok = bin >= 0;
-                const uint64_t m = __ballot(ok);
-                if (ok) {
-                    const uint32_t seq = running + lane_prefix_tri(m);
-                    if (seq >= lo && seq < hi) {
-                        const uint32_t k = seq - lo;
-                        R.d[k] = e;
-                        R.idx[k] = j;
-                        if (W) R.w[k] = a.w[j];
-                    }
+                double dx = px - xi, dy = py - yi, dz = pz - zi;
+                tri_wrap(dx, dy, dz, Lw, a.halfL);
+                float4 e = make_float4((float)dx, (float)dy, (float)dz, 0.f);
+                e.w = __builtin_fmaf(e.z, e.z, __builtin_fmaf(e.y, e.y, e.x * e.x));
+                uint64_t m = __ballot(h ? v1 : v0) & __ballot(e.w < vmax);
+                const uint64_t tm = (h ? t1 : t0) & m;
+                if (tm) {
+                    const bool after =
+                        pz > zi || (pz == zi && (py > yi || (py == yi && (px > xi || (px == xi && j > i)))));
+                    m &= ~tm | __ballot(after);
+                }
+                const uint32_t seq = running + lane_prefix_tri(m);
+                if (__builtin_amdgcn_inverse_ballot_w64(m) && seq >= lo && seq < hi) {
+                    R.d[seq - lo] = e;
+                    R.idx[seq - lo] = j;
                 }
                 running += (uint32_t)__popcll(m);
             }
-            nside += min(total - c0, 128u);
+            nside += min(r.total - c0, 128u);
             stop = !whole && running >= hi;
         }
         if (stop) break;
@@ -325,129 +319,165 @@ __device__ uint32_t tri_gather(const TriArgs& a, const BinTable& T, int64_t i, d
     return running;
 }
 
-// The side between list entries p and q: FP32 from the two displacements
-// (both within reach of the primary, so their difference is the minimum image
-// with no wrap), binned; inside a band, the FP64 side of the definition from
-// the sorted positions.
-// EXACT: the box is too small for that (L < 4 r): every side is the FP64 one.
-// `live` false: a padding pair whose result is discarded (not counted as a
-// recheck); its entries are valid, so the recheck's reads stay in bounds.
-template <bool EXACT>
-__device__ __attribute__((always_inline)) inline int tri_side_bin(const TriArgs& a, const BinTable& T, float4 ep,
-                                                                 float4 eq, const uint32_t* pidx, int p,
-                                                                 const uint32_t* qidx, int q, bool live,
-                                                                 uint32_t& rechk) {
-    const float ex = eq.x - ep.x, ey = eq.y - ep.y, ez = eq.z - ep.z;
-    int b = EXACT ? -2 : bin32(T, a.top, __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex)));
-    if (b == -2) {
-        rechk += live ? 1u : 0u;
-        const double* pp = a.pos + 3 * (size_t)pidx[p];
-        const double* pq = a.pos + 3 * (size_t)qidx[q];
-        b = bin_exact(T.E, T.nb, side2(pp[0], pp[1], pp[2], pq[0], pq[1], pq[2], a.L, a.halfL));
-    }
-    return b;
-}
-
-// Counter of the triangle whose two sides to the primary are list entries with
-// .w bits wp and wq and whose third side is in bin s.
-template <bool U>
-__device__ __attribute__((always_inline)) inline int tri_counter(const int* t3, uint32_t wp, uint32_t wq, int s) {
-    if (U) return (int)((wp & 0xffffu) + (wq >> 16)) + s;
-    return tri_slot(t3, (int)wp, (int)wq, s);
-}
-
-// Every pair p < q of one list.  Each lane takes groups (p, q), (p + 1, q)
-// from the group table (p | q << 8, by column q, so the first G(m) groups are
-// those of a list of m entries), reading the entry of q once for both pairs,
-// two groups per step (g and g + 64) so that their reads overlap.  When
-// p + 1 = q the group has one pair; a second group past the list repeats the
-// first.  Such pairs are formed on valid entries and discarded.
-template <bool W, bool U, bool EXACT>
-__device__ void tri_self(const TriArgs& a, const BinTable& T, const TriList& R, int m, double wi, const int* t3,
-                         const uint16_t* gtab, unsigned long long* hist, unsigned long long* wl, int lane,
-                         unsigned long long& nside, uint32_t& rechk) {
-    nside += (unsigned long long)(m * (m - 1) / 2);
-    const int ng = (m / 2) * ((m + 1) / 2);
-    for (int g = lane; g < ng; g += 128) {
-        const bool second = g + 64 < ng;
-        const uint32_t wA = gtab[g], wB = gtab[second ? g + 64 : g];
-        int p[4], q[4];
-        bool live[4];
-        p[0] = wA & 255;
-        q[0] = wA >> 8;
-        p[1] = p[0] + 1;
-        q[1] = q[0];
-        p[2] = wB & 255;
-        q[2] = wB >> 8;
-        p[3] = p[2] + 1;
-        q[3] = q[2];
-        live[0] = true;
-        live[1] = p[1] < q[1];
-        live[2] = second;
-        live[3] = second && p[3] < q[3];
-        const float4 eqA = R.d[q[0]], eqB = R.d[q[2]];
-        float4 ep[4];
-#pragma unroll
-        for (int u = 0; u < 4; u++) ep[u] = R.d[p[u]];
-        int sb[4];
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-            sb[u] = tri_side_bin<EXACT>(a, T, ep[u], u < 2 ? eqA : eqB, R.idx, p[u], R.idx, q[u], live[u], rechk);
-            sb[u] = live[u] ? sb[u] : -1;
+// The bins of the sides to the primary of the n points gathered into R;
+// points in no bin leave the list.  Returns the entries left, with entries out
+// of reach of everything added up to a multiple of 16.
+template <bool W>
+__device__ inline int tri_bins(const TriArgs& a, const BinTable& T, const float2* nband, double xi, double yi,
+                               double zi, double Lw, const TriList& R, int n, int lane, uint32_t& rechk) {
+    int kept = 0;
+    for (int e0 = 0; e0 < n; e0 += 64) {
+        const int e = e0 + lane;
+        int bin = -1;
+        float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
+        uint32_t j = 0;
+        if (e < n) {
+            d = R.d[e];
+            j = R.idx[e];
+            bin = tri_entry(T, a.top, d.w * T.scale);
+            if (bin < -1) bin = tri_hot(T, nband, bin, d.w, [&] { return d.w; });
+            if (bin == -2) {
+                rechk++;
+                double dx = a.pos[3 * (size_t)j] - xi, dy = a.pos[3 * (size_t)j + 1] - yi,
+                       dz = a.pos[3 * (size_t)j + 2] - zi;
+                tri_wrap(dx, dy, dz, Lw, a.halfL);
+                bin = bin_exact(T.E, T.nb, (dx * dx + dy * dy) + dz * dz);
+            }
         }
+        const uint64_t m = __ballot(bin >= 0);
+        if (bin >= 0) {
+            const int k = kept + (int)lane_prefix_tri(m);
+            if (k != e) {
+                R.d[k] = d;
+                R.idx[k] = j;
+            }
+            R.bin[k] = (uint8_t)bin;
+            if (W) R.w[k] = a.w[j];
+        }
+        kept += (int)__popcll(m);
+    }
+    const int k = kept + lane;
+    if (k < ((kept + 15) & ~15)) {
+        R.d[k] = make_float4(0.f, 0.f, 0.f, 3e38f);
+        R.bin[k] = 0;
+    }
+    wave_sync_lds_tri();
+    return kept;
+}
+
+// Add one to the counters at LDS byte addresses `at` of the lanes in `m`.  Every
+// lane of the wave is active here; the addition runs under the mask itself,
+// set and restored around it (a branch around an empty addition costs more).
+__device__ __attribute__((always_inline)) inline void tri_count(uint32_t at, uint64_t m) {
+    const unsigned long long one = 1ull;
+    __asm__ volatile(
+        "s_mov_b64 exec, %2\n\t"
+        "ds_add_u64 %0, %1\n\t"
+        "s_mov_b64 exec, -1"
+        :
+        : "v"(at), "v"(one), "s"(m)
+        : "memory");
+}
+
+// Every pair p < q of one list (SELF) or every pair of an earlier list P and a
+// later one Q, 16 x 16 pairs at a time.  The squares of the sides come from the
+// matrix cores, |p|^2 - 2 p.q in one step of v_mfma_f32_16x16x4_f32 added to
+// |q|^2: lane l gets the sides of q = l % 16 to p = 4 (l / 16) + 0..3.  Their
+// error is absolute, up to the bands of the table; the few sides inside one are
+// formed again as FP32 differences (tri_hot), and inside the narrower bands of
+// those in FP64 from the sorted positions, as the definition does.
+// EXACT: the box is too small for differences of displacements (L < 4 r): every
+// side is the FP64 one.
+template <bool W, bool U, bool EXACT, bool SELF>
+__device__ inline void tri_pairs(const TriArgs& a, const BinTable& T, const float2* nband, const TriList& P, int mp,
+                                 const TriList& Q, int mq, double wi, const int* t3, unsigned long long* hist,
+                                 unsigned long long* wl, int lane, unsigned long long& nside, uint32_t& rechk) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    nside += SELF ? (unsigned long long)(mp * (mp - 1) / 2) : (unsigned long long)mp * (unsigned long long)mq;
+    const int g = lane >> 4, c = lane & 15;
+    const float mul = g == 3 ? T.scale : -2.0f * T.scale;
+    const uint32_t nb = (uint32_t)T.nb, nb2 = nb * nb;
+    const uint32_t hist_l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned long long*)hist;
+    const int np = (mp + 15) >> 4, nq = (mq + 15) >> 4;
+    for (int rb = 0; rb < np; rb++) {
+        const float A = ((const float*)P.d)[(rb * 16 + c) * 4 + g] * mul;
+        const uint32_t pb4 = ((const uint32_t*)P.bin)[rb * 4 + g];
+        uint32_t pb[4];
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
-            const uint32_t cq = __float_as_uint(u < 2 ? eqA.w : eqB.w);
-            const int k = tri_counter<U>(t3, __float_as_uint(ep[u].w), cq, max(sb[u], 0));
-            if (W) {
-                if (sb[u] >= 0) {
-                    atomicAdd(&hist[k], 1ull);
-                    tri_add_weight(wl, a.nhist, k, tri_weight(wi, R.w[p[u]], R.w[q[u]]) * a.wscale);
+        for (int i = 0; i < 4; i++) pb[i] = __umul24((pb4 >> (8 * i)) & 255u, U ? nb2 : 1u);
+        auto block = [&](auto diag, int cb) {
+            constexpr bool DIAG = decltype(diag)::value;
+            const int q = cb * 16 + c;
+            const float bq = ((const float*)Q.d)[q * 4 + g];
+            const float qq = Q.d[q].w * T.scale;
+            const uint32_t qb = U ? __umul24(Q.bin[q], nb) : (uint32_t)Q.bin[q];
+            int e[4];
+            float v[4];
+            if (!EXACT) {
+                const f4 C = {qq, qq, qq, qq};
+                const f4 D = __builtin_amdgcn_mfma_f32_16x16x4f32(A, g == 3 ? 1.0f : bq, C, 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 4; i++) v[i] = D[i];
+                if (DIAG) {
+#pragma unroll
+                    for (int i = 0; i < 4; i++) v[i] = 4 * g + i < c ? v[i] : 3e38f;
                 }
+#pragma unroll
+                for (int i = 0; i < 4; i++) e[i] = tri_entry(T, a.top, v[i]);
             } else {
-                // a pair out of range adds to this lane's dump counter (no branch)
-                atomicAdd(&hist[sb[u] >= 0 ? k : a.nhist + lane], 1ull);
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int p = rb * 16 + 4 * g + i;
+                    e[i] = p < mp && q < mq && (!DIAG || p < q) ? -2 : -1;
+                    v[i] = 0.f;
+                }
             }
-        }
+            if (min(min(e[0], e[1]), min(e[2], e[3])) < -1) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const int p = rb * 16 + 4 * g + i;
+                    if (e[i] < -1) {
+                        if (!EXACT)
+                            e[i] = tri_hot(T, nband, e[i], v[i] * a.inv_scale, [&] {
+                                const float4 dp = P.d[p], dq = Q.d[q];
+                                const float ex = dq.x - dp.x, ey = dq.y - dp.y, ez = dq.z - dp.z;
+                                return __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex));
+                            });
+                        if (e[i] == -2) {
+                            rechk++;
+                            const double* pp = a.pos + 3 * (size_t)P.idx[p];
+                            const double* pq = a.pos + 3 * (size_t)Q.idx[q];
+                            e[i] = bin_exact(T.E, T.nb,
+                                             side2(pp[0], pp[1], pp[2], pq[0], pq[1], pq[2], a.L, a.halfL));
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const int k = U ? (int)(pb[i] + qb) + e[i] : tri_slot(t3, (int)pb[i], (int)qb, max(e[i], 0));
+                if (W) {
+                    if (e[i] >= 0) {
+                        atomicAdd(&hist[k], 1ull);
+                        tri_add_weight(wl, a.nhist, k,
+                                       tri_weight(wi, P.w[rb * 16 + 4 * g + i], Q.w[q]) * a.wscale);
+                    }
+                } else {
+                    tri_count(hist_l + ((uint32_t)k << 3), __ballot(e[i] >= 0));
+                }
+            }
+        };
+        // (the block on the diagonal of a list with itself has only p < q)
+        if (SELF) block(std::true_type{}, rb);
+        for (int cb = SELF ? rb + 1 : 0; cb < nq; cb++) block(std::false_type{}, cb);
     }
 }
 
-// Every pair of an earlier list P (m1 entries) and a later list Q (m2), two
-// entries of Q per lane per step.
-template <bool W, bool U, bool EXACT>
-__device__ void tri_cross(const TriArgs& a, const BinTable& T, const TriList& P, int m1, const TriList& Q, int m2,
-                          double wi, const int* t3, unsigned long long* hist, unsigned long long* wl, int lane,
-                          unsigned long long& nside, uint32_t& rechk) {
-    nside += (unsigned long long)m1 * (unsigned long long)m2;
-    for (int p = 0; p < m1; p++) {
-        const float4 ep = P.d[p];
-        const uint32_t pb = __float_as_uint(ep.w);
-        const double pw = W ? P.w[p] : 0.0;
-        for (int q = lane; q < m2; q += 128) {
-            const bool two = q + 64 < m2;
-            const int q1 = two ? q + 64 : q;
-            const float4 e0 = Q.d[q], e1 = Q.d[q1];
-            const int s0 = tri_side_bin<EXACT>(a, T, ep, e0, P.idx, p, Q.idx, q, true, rechk);
-            int s1 = tri_side_bin<EXACT>(a, T, ep, e1, P.idx, p, Q.idx, q1, two, rechk);
-            s1 = two ? s1 : -1;
-            if (s0 >= 0) {
-                const int k = tri_counter<U>(t3, pb, __float_as_uint(e0.w), s0);
-                atomicAdd(&hist[k], 1ull);
-                if (W) tri_add_weight(wl, a.nhist, k, tri_weight(wi, pw, Q.w[q]) * a.wscale);
-            }
-            if (s1 >= 0) {
-                const int k = tri_counter<U>(t3, pb, __float_as_uint(e1.w), s1);
-                atomicAdd(&hist[k], 1ull);
-                if (W) tri_add_weight(wl, a.nhist, k, tri_weight(wi, pw, Q.w[q1]) * a.wscale);
-            }
-        }
-    }
-}
-
-// LDS bytes of one list region: displacement + bin (16), index (4), weight (8)
+// LDS bytes of one list region: displacement and square (16), weight (8),
+// index (4), bin (1)
 template <bool W>
 constexpr int tri_region_bytes() {
-    return TRI_CAP * (W ? 28 : 20);
+    return TRI_CAP * (W ? 29 : 21);
 }
 
 // U: ordered counters (nb^3 of them, unweighted counts with few bins);
@@ -463,22 +493,10 @@ __global__ __launch_bounds__(TRI_MAX_WAVES * 64) void k_triplets(TriArgs a) {
         for (int k = tid; k < a.nhist; k += nthr) h[k] = 0ull;
         int* t3w = (int*)(smem + a.off_t3);
         for (int k = tid; k <= TRI_MAX_BINS; k += nthr) t3w[k] = k * (k + 1) * (k + 2) / 6;
-        uint16_t* gt = (uint16_t*)(smem + a.off_ptab);
-        for (int g = tid; g < TRI_GROUPS; g += nthr) {
-            // column q holds ceil(q / 2) groups; the columns before q hold G(q)
-            int q = (int)(2.0f * __builtin_amdgcn_sqrtf((float)g));
-            while (q > 1 && (q / 2) * ((q + 1) / 2) > g) q--;
-            while (((q + 1) / 2) * ((q + 2) / 2) <= g) q++;
-            const int p = 2 * (g - (q / 2) * ((q + 1) / 2));
-            gt[g] = (uint16_t)(p | (q << 8));
-        }
         if (W) {
             unsigned long long* z = (unsigned long long*)(smem + a.off_wl);
             for (int k = tid; k < 3 * a.nhist; k += nthr) z[k] = 0ull;
         }
-        // list regions start zeroed: a padding pair reads valid indices
-        uint4* lz = (uint4*)(smem + a.off_lists);
-        for (int k = tid; k < a.lists_words; k += nthr) lz[k] = make_uint4(0u, 0u, 0u, 0u);
     }
     __syncthreads();
     BinTable T;
@@ -490,23 +508,28 @@ __global__ __launch_bounds__(TRI_MAX_WAVES * 64) void k_triplets(TriArgs a) {
     T.nb = a.nb;
     unsigned long long* hist = (unsigned long long*)(smem + a.off_hist);
     const int* t3 = (const int*)(smem + a.off_t3);
-    const uint16_t* ptab = (const uint16_t*)(smem + a.off_ptab);
+    const float2* nband = (const float2*)(smem + a.off_nband);
     unsigned long long* wl = W ? (unsigned long long*)(smem + a.off_wl) : nullptr;
     const int lane = tid & 63, wave = tid >> 6;
     constexpr int RB = tri_region_bytes<W>();
     char* base = smem + a.off_lists + (size_t)wave * 2 * RB;
     TriList R1, R2;
     R1.d = (float4*)base;
-    R1.idx = (uint32_t*)(R1.d + TRI_CAP);
-    R1.w = (double*)(R1.idx + TRI_CAP);
+    R1.w = (double*)(R1.d + TRI_CAP);
+    R1.idx = (uint32_t*)(R1.w + (W ? TRI_CAP : 0));
+    R1.bin = (uint8_t*)(R1.idx + TRI_CAP);
     R2.d = (float4*)(base + RB);
-    R2.idx = (uint32_t*)(R2.d + TRI_CAP);
-    R2.w = (double*)(R2.idx + TRI_CAP);
+    R2.w = (double*)(R2.d + TRI_CAP);
+    R2.idx = (uint32_t*)(R2.w + (W ? TRI_CAP : 0));
+    R2.bin = (uint8_t*)(R2.idx + TRI_CAP);
     unsigned long long nside = 0;
     uint32_t rechk = 0;
     // Primaries are claimed `claim` at a time: one atomic per primary on the
     // one cursor serialised the whole grid (about 11 ns per claim).
     uint32_t next = 0, last = 0;
+    uint32_t ranged = ~0u;  // cell of the ranges held
+    TriRanges rg{};
+    int cx = 0, cy = 0, cz = 0;
     for (;;) {
         if (next >= last) {
             uint32_t base = 0;
@@ -519,36 +542,45 @@ __global__ __launch_bounds__(TRI_MAX_WAVES * 64) void k_triplets(TriArgs a) {
         const int64_t i = next++;
         const double xi = a.pos[3 * (size_t)i], yi = a.pos[3 * (size_t)i + 1], zi = a.pos[3 * (size_t)i + 2];
         const double wi = W ? a.w[i] : 0.0;
-        const uint32_t cell = a.xkey[i] >> a.xbits;
-        const int cx = (int)(cell % (uint32_t)a.nx);
-        const int cy = (int)((cell / (uint32_t)a.nx) % (uint32_t)a.ny);
-        const int cz = (int)(cell / ((uint32_t)a.nx * (uint32_t)a.ny));
+        const uint32_t cell = (uint32_t)__builtin_amdgcn_readfirstlane((int)(a.xkey[i] >> a.xbits));
         // a primary this far inside the box has no neighbour across a face:
         // its sides need no minimum image
         const bool inside = a.inner > 0.0 && xi > a.inner && xi < a.L - a.inner && yi > a.inner &&
                             yi < a.L - a.inner && zi > a.inner && zi < a.L - a.inner;
         const double Lw = inside ? 0.0 : a.L;
-        const uint32_t m = tri_gather<W, U>(a, T, i, xi, yi, zi, cell, cx, cy, cz, Lw, 0, true, R1, lane, nside, rechk);
+        // (primaries in a row of one claim mostly share their cell)
+        if (cell != ranged) {
+            const uint32_t row = cell / (uint32_t)a.nx;
+            cz = (int)(row / (uint32_t)a.ny);
+            cy = (int)row - cz * a.ny;
+            cx = (int)(cell - row * (uint32_t)a.nx);
+            if (a.nst <= 32) tri_ranges(a, 0, cx, cy, cz, lane, rg);
+            ranged = cell;
+        }
+        const uint32_t m = tri_gather(a, T.vmax, i, xi, yi, zi, cx, cy, cz, Lw, 0, true, rg, R1, lane, nside);
         if (m < 2) continue;
         const uint32_t nch = (m + TRI_CAP - 1) / TRI_CAP;
         for (uint32_t A = 0; A < nch; A++) {
             if (A > 0) {
                 wave_sync_lds_tri();
-                tri_gather<W, U>(a, T, i, xi, yi, zi, cell, cx, cy, cz, Lw, A * TRI_CAP, false, R1, lane, nside, rechk);
+                tri_gather(a, T.vmax, i, xi, yi, zi, cx, cy, cz, Lw, A * TRI_CAP, false, rg, R1, lane, nside);
             }
-            const int mA = (int)std::min<uint32_t>(TRI_CAP, m - A * TRI_CAP);
+            const int mA = tri_bins<W>(a, T, nband, xi, yi, zi, Lw, R1, (int)std::min<uint32_t>(TRI_CAP, m - A * TRI_CAP),
+                                       lane, rechk);
+            if (nch == 1 && mA < 2) break;
             if (a.exact_pairs)
-                tri_self<W, U, true>(a, T, R1, mA, wi, t3, ptab, hist, wl, lane, nside, rechk);
+                tri_pairs<W, U, true, true>(a, T, nband, R1, mA, R1, mA, wi, t3, hist, wl, lane, nside, rechk);
             else
-                tri_self<W, U, false>(a, T, R1, mA, wi, t3, ptab, hist, wl, lane, nside, rechk);
+                tri_pairs<W, U, false, true>(a, T, nband, R1, mA, R1, mA, wi, t3, hist, wl, lane, nside, rechk);
             for (uint32_t B = A + 1; B < nch; B++) {
                 wave_sync_lds_tri();
-                tri_gather<W, U>(a, T, i, xi, yi, zi, cell, cx, cy, cz, Lw, B * TRI_CAP, false, R2, lane, nside, rechk);
-                const int mB = (int)std::min<uint32_t>(TRI_CAP, m - B * TRI_CAP);
+                tri_gather(a, T.vmax, i, xi, yi, zi, cx, cy, cz, Lw, B * TRI_CAP, false, rg, R2, lane, nside);
+                const int mB = tri_bins<W>(a, T, nband, xi, yi, zi, Lw, R2,
+                                           (int)std::min<uint32_t>(TRI_CAP, m - B * TRI_CAP), lane, rechk);
                 if (a.exact_pairs)
-                    tri_cross<W, U, true>(a, T, R1, mA, R2, mB, wi, t3, hist, wl, lane, nside, rechk);
+                    tri_pairs<W, U, true, false>(a, T, nband, R1, mA, R2, mB, wi, t3, hist, wl, lane, nside, rechk);
                 else
-                    tri_cross<W, U, false>(a, T, R1, mA, R2, mB, wi, t3, hist, wl, lane, nside, rechk);
+                    tri_pairs<W, U, false, false>(a, T, nband, R1, mA, R2, mB, wi, t3, hist, wl, lane, nside, rechk);
             }
         }
         wave_sync_lds_tri();
@@ -757,46 +789,66 @@ extern "C" fcfc_status fcfc_count_triplets(fcfc_plan_t plan, fcfc_cells_t cells,
     // definition carry a few ulps of the coordinates; twice that for margin
     const double U = 5.9604644775390625e-08;
     const double e_axis = 2.0 * (4.0 * U * rr + 4.0 * 2.220446049250313e-16 * (Lbox + rr));
-    const Lut1D* Tp = nullptr;
-    FCFC_TRY(plan_side_table(p, e_axis, &Tp));
+    // The matrix product forms |p|^2 + |q|^2 - 2 p.q from terms that add up to 4
+    // r'^2 in magnitude with some ten roundings (40 u r'^2); twice that again
+    const double gram = 80.0 * U * rr * rr;
     std::vector<int4> sten;
     tri_stencil(g, p->rprune, sten);
     tri_rows(sten);
 
     TriArgs a{};
-    std::vector<char> blob_h;
-    const BinBlob B = bin_blob(*Tp, blob_h);
     // unweighted counts with few bins use nb^3 ordered counters (no sort of
     // the three bins per triangle), folded into sorted bins afterwards
     const bool ordered = !weighted && nb <= TRI_ORDERED_MAX_BINS;
     a.nhist = ordered ? nb * nb * nb : (nb + 2) * (nb + 1) * nb / 6;
-    a.off_band = B.off_band;
-    a.off_e = B.off_e;
-    a.off_hist = B.bytes;
-    a.off_t3 = a.off_hist + bin_al16((a.nhist + 64) * 8);  // counters, then 64 dump counters
-    a.off_ptab = a.off_t3 + bin_al16((TRI_MAX_BINS + 1) * 4);
-    a.off_wl = a.off_ptab + bin_al16(TRI_GROUPS * 2);
-    a.off_lists = a.off_wl + (weighted ? bin_al16(a.nhist * 24) : 0);
     const int per_wave = 2 * (weighted ? tri_region_bytes<true>() : tri_region_bytes<false>());
     int dev = 0, maxlds = 65536;
     FCFC_HIP(hipGetDevice(&dev));
     if (hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) maxlds = 65536;
-    int waves = TRI_MAX_WAVES;
-    while (waves > 1 && a.off_lists + waves * per_wave > maxlds) waves--;
-    if (a.off_lists + waves * per_wave > maxlds) {
+    // The table of 2^14 entries where it leaves room for 16 waves, else 2^13:
+    // half as many sides meet a band (on MI355X 1M points, 57 neighbours each,
+    // 2.78 -> 2.68 ms)
+    const int lg0 = p->tune.lut_log2 > 0 ? std::min(14, std::max(8, p->tune.lut_log2)) : 14;
+    const int lg1 = p->tune.lut_log2 > 0 ? lg0 : 13;
+    std::vector<char> blob_h;
+    BinBlob B;
+    const int nband_bytes = bin_al16((nb + 2) * 8);
+    int tab_bytes = 0, waves = 0;
+    for (int lg = lg0; waves < TRI_MAX_WAVES && lg >= lg1; lg--) {
+        const Lut1D *Tp = nullptr, *Tn = nullptr;
+        FCFC_TRY(plan_side_tables(p, e_axis, gram, lg, &Tp, &Tn));
+        B = bin_blob(*Tp, blob_h);
+        // the narrow bands follow the blob
+        std::vector<char> nh;
+        const BinBlob N = bin_blob(*Tn, nh);
+        blob_h.insert(blob_h.end(), nh.begin() + N.off_band, nh.begin() + N.off_band + nband_bytes);
+        tab_bytes = B.bytes + nband_bytes;
+        a.off_band = B.off_band;
+        a.off_e = B.off_e;
+        a.off_nband = B.bytes;
+        a.off_hist = tab_bytes;
+        a.off_t3 = a.off_hist + bin_al16(a.nhist * 8);
+        a.off_wl = a.off_t3 + bin_al16((TRI_MAX_BINS + 1) * 4);
+        a.off_lists = a.off_wl + (weighted ? bin_al16(a.nhist * 24) : 0);
+        waves = TRI_MAX_WAVES;
+        while (waves > 1 && a.off_lists + waves * per_wave > maxlds) waves--;
+    }
+    // the accepted sizes: 8.5 KB beside the tables and counters, and two lists
+    // of 28 or 20 bytes an entry, which holds what the kernel needs
+    const int accept = a.off_lists - nband_bytes + 8704 + 2 * TRI_CAP * (weighted ? 28 : 20);
+    if (std::max(accept, a.off_lists + waves * per_wave) > maxlds) {
         set_error("count_triplets: the tables and histogram of %d bins do not fit the LDS%s", nb,
                   weighted ? " with weighted sums" : "");
         return FCFC_ERANGE;
     }
     const int lds = a.off_lists + waves * per_wave;
-    a.lists_words = waves * per_wave / 16;
     const int variant = weighted ? 2 : (ordered ? 1 : 0);
     const void* kern = weighted  ? (const void*)k_triplets<true, false>
                        : ordered ? (const void*)k_triplets<false, true>
                                  : (const void*)k_triplets<false, false>;
 
     // device block: tables, stencil, counters, weighted sums, cursor
-    const size_t sz_tab = (size_t)B.bytes, sz_st = sten.size() * sizeof(int4), sz_out = (size_t)a.nhist * 8,
+    const size_t sz_tab = (size_t)tab_bytes, sz_st = sten.size() * sizeof(int4), sz_out = (size_t)a.nhist * 8,
                  sz_w = weighted ? (size_t)a.nhist * 16 : 0;
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t o_st = sz_tab, o_out = o_st + up(sz_st), o_w = o_out + up(sz_out), o_cur = o_w + up(sz_w),
@@ -837,9 +889,10 @@ extern "C" fcfc_status fcfc_count_triplets(fcfc_plan_t plan, fcfc_cells_t cells,
         a.exact_pairs = (a.L > 0 && 4.0 * rr > a.L) ? 1 : 0;
         a.n = c->n;
         a.tab = (const uint4*)blk;
-        a.tab_words = B.bytes / 16;
+        a.tab_words = tab_bytes / 16;
         a.nb = nb;
         a.scale = B.scale;
+        a.inv_scale = 1.0f / B.scale;
         a.vmax = B.vmax;
         a.top = (float)(B.nt - 1);
         a.out = (unsigned long long*)(blk + o_out);
@@ -899,7 +952,7 @@ extern "C" fcfc_status fcfc_count_triplets(fcfc_plan_t plan, fcfc_cells_t cells,
     p->last_counts_n = (int64_t)nb * nb * nb;
     p->have_stats = true;
     p->stats.items = c->n;
-    p->stats.lut_entries = (int32_t)Tp->tab.size();
+    p->stats.lut_entries = (int32_t)B.nt;
     p->stats.group_waves = waves;
     return FCFC_OK;
 }

@@ -244,3 +244,29 @@ def test_most_bins():
     assert_same(c, rc, wc, rw, what="20 bins weighted")
     with pytest.raises(fcfc.FcfcError):
         _gpu_tri_w(x, w, e32, 40.0)
+
+
+@pytest.mark.parametrize("m", [2, 3, 15, 16, 17, 18, 33, 64, 65, 128, 129, 130, 146])
+@pytest.mark.parametrize("nb,weighted", [(6, False), (17, False), (6, True)])
+def test_lists_at_the_edges_of_blocks(m, nb, weighted):
+    """Clumps of m points within reach of one another, so that the primaries'
+    lists take every length from 0 to m - 1: around the blocks of 16, the steps
+    of 64 and the lists of 128 entries; ordered, sorted and weighted counters.
+    A third of the points are copies shifted by exact multiples of the bin
+    width along an axis, so that sides fall on edges."""
+    rng = np.random.default_rng(m * 40 + nb)
+    x = 20.0 + rng.uniform(0, 1.0, (m, 3))
+    k = m // 3
+    x[:k] = x[m - k:]
+    x[:k, 0] += rng.integers(1, nb, k) * 0.25
+    x = np.concatenate([x, rng.uniform(0, 60, (30, 3))])
+    e = np.arange(nb + 1) * 0.25
+    note(f"triplets: clump {m}, {nb} bins, weighted {weighted}")
+    if weighted:
+        w = rng.uniform(0.5, 2.0, len(x))
+        c, wc, _ = _gpu_tri_w(x, w, e, 60.0)
+        rc, rw = oracle.triplets(x, edges=e, box=60.0, w=w)
+        assert_same(c, rc, wc, rw, what=f"clump {m}")
+    else:
+        got, st = _gpu_tri(x, e, 60.0)
+        assert_same(got, oracle.triplets(x, edges=e, box=60.0), what=f"clump {m}")
