@@ -123,7 +123,7 @@ static void set_linear(const Plan* p, CountArgs& a) {
     const double s1 = p->e1.back() * 1.01, o1 = 1.0 - p->e1[0] / ds1;
     a.e_unit = (float)(u / p->e_axis * (1.0 + 1e-6));
     a.l1c = (float)(1.0 / ds1);
-    a.l1o = (float)o1;
+    a.l1o = (float)(o1 - 1.0);
     const double tr = trans_rel_bound();
     const double abs1 = M * (p->em1.A + p->em1.C * s1) / 2.0 + (tr + 4.0 * u) * s1;
     a.l1t = (float)(1.01 * (abs1 + of1) / ds1 + 8.0 * u * (p->n1 + 1.0 + fabs(o1)));
@@ -131,7 +131,7 @@ static void set_linear(const Plan* p, CountArgs& a) {
     if (two) {
         const double o2 = 1.0 - p->e2[0] / ds2, p2 = p->e2.back() * 1.01;
         a.l2c = (float)(1.0 / ds2);
-        a.l2o = (float)o2;
+        a.l2o = (float)(o2 - 1.0);
         a.l2t = (float)(1.01 * (M * p->e_pi + M * (tr + 8.0 * u) * p2 + of2) / ds2 + 8.0 * u * (p->n2 + 1.0 + fabs(o2)));
     }
     // bands wider than a quarter of a bin would recheck everything: the tables then
@@ -342,6 +342,7 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
     a.L = g.L;
     a.halfL = g.L * 0.5;
     a.mu_n = (float)p->n2;
+    a.mu_c = a.mu_n * (1.0f - mu_shrink(p->los == FCFC_LOS_MIDPOINT));
     // pairs closer than sqrt(d2small) are always rechecked: the band then spans a whole mu bin
     a.tolA = std::max(p->mu_tolA, 1.01f * sqrtf(p->d2small));
     a.tolC = p->mu_tolC;

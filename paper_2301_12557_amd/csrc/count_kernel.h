@@ -117,13 +117,13 @@ struct CountArgs {
     // for (s_perp, pi)), squared reach from the box of the A points, second
     // axis, and the margins
     float f_t2, f_cull2, f_u, f_reach, f_slack, f_uslack, f_uerr, f_ts;
-    // uniform edges: x = s l1c + l1o (and |pi| l2c + l2o) is the bin plus one
-    // plus a fraction, good to l1a / s + l1t (l2t)
+    // uniform edges: x = s l1c + l1o (and |pi| l2c + l2o) is the bin plus a
+    // fraction, good to l1a / s + l1t (l2t)
     int lin;
     float l1c, l1o, l1a, l1t, l2c, l2o, l2t;
     float e_unit;  // u over the error of one displacement component
     float xstep;   // a row's points are sorted by x to this
-    float mu_n, tolA, tolC;
+    float mu_n, mu_c, tolA, tolC;  // mu_c: mu_n less mu_shrink
     int mu_top_closed;
     WeightFmt wf;
     int copies;
@@ -324,6 +324,21 @@ struct KConst {
     WeightFmt wf;
 };
 
+// largest integer at or below x (0 for a NaN) in one instruction
+__device__ inline int floor_i(float x) {
+    int r;
+    __asm__("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// With computed bins mu n2 is formed with n2 times one minus this, more than the
+// rounding of mu (two or three reciprocal square roots of 4.8e-7 at most and a
+// few products, 0.8e-6 along z and 1.6e-6 to the mid-point), so that mu = 1 needs
+// no clamp; the mu bands are wider by as much.  (With the bins rounded down
+// instead of truncated and shifted: on MI355X 16 mocks of 100,000 to 500,000
+// points 36.5 -> 35.7 ms.)
+__host__ __device__ constexpr float mu_shrink(bool mid) { return mid ? 0x1p-18f : 0x1p-19f; }
+
 // Add a pair of weight p to bin `flat` of a weighted count.  p 2^S is an
 // integer q (the host chose S), |q| <= 2^qb; with q = i 2^k + r, |r| <= 2^(k-1),
 // the bin holds two 64-bit words,
@@ -487,7 +502,8 @@ __device__ __attribute__((always_inline)) inline void bin_queue(ArgsRef a, const
         const float proj_n = MID ? fabsf(dot) * (__builtin_amdgcn_rsqf(lsq) * k.mu_n) : fabsf(dz) * k.mu_n;
         rs = __builtin_amdgcn_rsqf(d2);
         const float mun = proj_n * rs;
-        b2 = min((int)mun, k.n2 - 1);
+        // (with computed bins mu_n is a little below n2, so that mun stays below n2)
+        b2 = LIN ? (int)mun : min((int)mun, k.n2 - 1);
         // distance to the nearest interior mu edge (edges 0 and n need no recheck: mu
         // >= 0 always, and mu = 1 belongs to the last bin); not a number at zero
         // separation, which is a recheck too
@@ -506,13 +522,13 @@ __device__ __attribute__((always_inline)) inline void bin_queue(ArgsRef a, const
                 v1 = __builtin_fmaf(dy, dy, dx * dx);
             }
             const float x2 = __builtin_fmaf(p, k.l2c, k.l2o);
-            b2 = (int)x2 - 1;
+            b2 = floor_i(x2);
             near2 = __builtin_amdgcn_ballot_w64(!(fabsf(x2 - rintf(x2)) >= c.t2));
             in2 = __builtin_amdgcn_ballot_w64((uint32_t)b2 < (uint32_t)k.n2);
         }
         if (KIND != FCFC_BIN_S_MU) rs = __builtin_amdgcn_rsqf(v1);
         const float x1 = __builtin_fmaf(v1 * rs, k.l1c, k.l1o);
-        const int b1 = (int)x1 - 1;
+        const int b1 = floor_i(x1);
         // |s32 - s| is bounded by the displacement's error; the mid-point s_perp^2 is a
         // difference, good to an absolute error: that over s_perp
         const float tol1 = SPI && MID ? __builtin_fmaf(c.t1a, rs, c.t1) : c.t1;
@@ -735,11 +751,11 @@ void k_count(const CountArgs* argp) {
     k.scale2 = a.scale2;
     k.vmax1 = a.vmax1;
     k.vmax2 = a.vmax2;
-    k.mu_n = a.mu_n;
+    k.mu_n = LIN ? a.mu_c : a.mu_n;
     k.mu_nm1 = a.mu_n - 1.0f;
     // one mu bin has no interior edge: nothing is near one
     k.tolA = a.n2 > 1 ? a.tolA : 0.0f;
-    k.tolC = a.n2 > 1 ? a.tolC : 0.0f;
+    k.tolC = a.n2 > 1 ? a.tolC + (LIN ? 1.01f * mu_shrink(MID) * a.mu_n : 0.0f) : 0.0f;
     k.tolC_v = k.tolC;
     __asm__ volatile("" : "+v"(k.tolC_v));
     k.side32 = a.side32;

@@ -135,3 +135,24 @@ def test_weight_ranges(ratio, sign):
     for tune in ({}, {"flush_log2": 8}):
         check_case("weights", x, kind="smu", edges1=synth.linear_edges(0, 15, 6), edges2=synth.mu_edges(5), los="z",
                    box=60.0, w1=w, **tune)
+
+
+@pytest.mark.parametrize("n2", [1, 2, 3, 7, 100, 120, 1000])
+@pytest.mark.parametrize("los", ["z", "mid"])
+def test_pairs_along_and_across_the_line_of_sight(n2, los):
+    """mu = 1 and mu = 0 exactly and a few ulps off, separations on, below and above the edges."""
+    rng = np.random.default_rng(n2)
+    base = rng.uniform(0, 40.0, (60, 3))
+    step = np.repeat(rng.integers(1, 12, 60)[:, None] * 0.5, 3, axis=1)
+    along = base + step * [0.0, 0.0, 1.0]
+    across = base + step * [1.0, 0.0, 0.0]
+    near = along + rng.choice([0.0, 1e-12, 1e-7, 1e-5], (60, 3))
+    x = np.concatenate([base, along, across, near])
+    if los == "mid":  # pairs on a line through the observer
+        d = rng.normal(size=(60, 3)) * 0.1 + [0.0, 0.0, 1.0]
+        d /= np.linalg.norm(d, axis=1)[:, None]
+        x = np.concatenate([x + [0.0, 0.0, 300.0], d * 310.0, d * (310.0 + step[:, :1])])
+    x = np.mod(x, 50.0) if los == "z" else x
+    for lo in (0.0, 1.0):
+        check_case("mu ends", x, kind="smu", edges1=synth.linear_edges(lo, 6, 10), edges2=synth.mu_edges(n2), los=los,
+                   box=50.0 if los == "z" else 0.0)
