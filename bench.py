@@ -75,7 +75,7 @@ def workload(name, weighted):
     return w, desc
 
 
-def measured_traffic(kernel_variant, sources=("count.hip",), key="count_hip_sha256_16"):
+def measured_traffic(kernel_variant, sources=("count_kernel.h", "count.hip"), key="src_sha256_16"):
     """HBM bytes per launch of a kernel from a committed rocprofv3 FETCH_SIZE /
     WRITE_SIZE summary (profiles/*_traffic.md), if it was taken on the current
     kernel sources and the same kernel variant; else None."""

@@ -92,7 +92,8 @@ typedef struct {
     int32_t order;           /* FCFC_ORDER_* */
     int32_t record_timing;   /* 1: record per-item GPU time (training data) */
     int32_t n_hint;          /* expected catalogue size, for automatic choices */
-    int32_t lut_log2;        /* log2 of the look-up table length target, 10..15 */
+    int32_t lut_log2;        /* log2 of the look-up table length target, 10..15 (pair counts on
+                                uniform edges read no table) */
     int32_t group_waves;     /* wavefronts per counting workgroup, 1..16 (0: as many as fit) */
     int32_t shard_count;     /* 0 or 1: the whole work list; G > 1: count one of G shards */
     int32_t shard_index;     /* the shard counted, 0..G-1: ordered items i with i % G == index */
@@ -112,7 +113,8 @@ typedef struct {
 /* Statistics of the last count on a plan (host copy; see fcfc_plan_stats). */
 typedef struct {
     int64_t items;           /* work items (A tile x B row piece) */
-    int64_t candidates;      /* pair separations evaluated in FP32 */
+    int64_t candidates;      /* pair separations evaluated in FP32 (B points beyond reach of the
+                                box around 64 A points are dropped before) */
     int64_t rechecks;        /* pairs re-evaluated in FP64 near an edge */
     int64_t in_range;        /* pairs counted (sum of the histogram) */
     int64_t cells;           /* grid cells */
@@ -121,7 +123,8 @@ typedef struct {
     double cell_side;        /* cell side length */
     double kernel_ms;        /* duration of the counting kernel (HIP events) */
     double band_d2_rel;      /* widest FP32 error band, relative to its edge */
-    int32_t lut_entries;     /* squared-separation look-up table length */
+    int32_t lut_entries;     /* squared-separation look-up table length; 0 where every axis has
+                                uniform edges and bins are computed */
     int32_t wg_per_cu;       /* resident counting workgroups per CU */
     int32_t order_used;      /* FCFC_ORDER_* the work list actually ran in */
     int32_t group_waves;     /* wavefronts per counting workgroup */
