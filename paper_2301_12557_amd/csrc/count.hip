@@ -230,9 +230,10 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
         return lds_for(waves) <= maxlds;
     };
     // The larger look-up tables (fewer entries that meet a band) are used
-    // whenever they keep as many waves resident: on MI355X they ran C1 0.34
-    // -> 0.26 ms and unweighted C2 5.6 -> 5.3 ms, while costing the weighted
-    // C2 kernel two of its 16 waves (7.5 -> 7.8 ms) where they are not used.
+    // whenever they keep as many waves resident: on MI355X, when uniform edges
+    // read tables too, they ran 20,000 points in s 0.34 -> 0.26 ms and 1M in
+    // (s, mu) 5.6 -> 5.3 ms, while costing the weighted count of those two of
+    // its 16 waves (7.5 -> 7.8 ms), where they are not used.
     const Lut1D* T1 = &p->lut1;
     const Lut1D* T2 = &p->lut2;
     int shared_bytes = lin ? shared_for(0, 0) : shared_for((int)T1->tab.size(), two ? (int)T2->tab.size() : 0);
