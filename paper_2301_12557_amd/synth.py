@@ -207,20 +207,24 @@ def mock(m, n, L=1000.0, ngrid=256):
 
 
 def _running_sum_torch(rho, ncol):
-    """Running sum of the FP64 values rho, whose length is a multiple of ncol,
+    """Running sum of the FP64 values rho >= 0, whose number is a multiple of ncol,
     with the same bits on every call.  torch.cumsum over one long row on the GPU
     adds the sums of its blocks in the order in which they happen to finish: over
     60 repeats 12 to 14 million of 256^3 entries changed in their last bits, which
     now and then moves a point drawn from them to the next cell (one such point
     changed 13 of 50 bins of a count of 10 million).  Here rows of ncol are summed
-    each by itself, in a fixed order, and the sums of the rows before are added up
-    on the host in extended precision, so that every entry is within two
-    roundings of the exact sum."""
+    each by itself, in a fixed order, and the rows before are added on the host.
+    For that, values are cut at 2^-40 of the largest: the upper parts of up to
+    2^24 values have exact sums in extended precision, in any order, and the
+    lower ones are too small for their roundings to matter."""
     import torch
     rows = torch.cumsum(rho.reshape(-1, ncol), 1)
-    before = np.cumsum(rows[:, -1].cpu().numpy().astype(np.longdouble))
-    before = np.concatenate([[0.0], before[:-1].astype(np.float64)])
-    return (rows + torch.from_numpy(before).to(rho.device)[:, None]).reshape(-1)
+    step = float(np.ldexp(1.0, int(np.frexp(float(rho.max()))[1]) - 40))
+    hi = torch.floor(rho / step) * step
+    before = np.zeros(rows.shape[0], dtype=np.longdouble)
+    for part in (hi, rho - hi):
+        before[1:] += np.cumsum(part.reshape(-1, ncol).sum(1).cpu().numpy().astype(np.longdouble))[:-1]
+    return (rows + torch.from_numpy(before.astype(np.float64)).to(rho.device)[:, None]).reshape(-1)
 
 
 def lognormal_box_torch(n, L, seed, device="cuda", ngrid=256, slope=-1.5, sigma=1.0):

@@ -20,9 +20,13 @@ def _check_sum(rho, ngrid, repeats):
     for _ in range(repeats):
         assert torch.equal(synth._running_sum_torch(rho, ngrid), first)
     # a row of ngrid adds up its values with at most ngrid roundings of the row's own
-    # sum; the rows before it are summed in extended precision and rounded once, and
-    # the addition of the two rounds once more
-    want = np.cumsum(rho.cpu().numpy().astype(np.longdouble))
+    # sum; the sum of the rows before it is exact but for one rounding, and the
+    # addition of the two rounds once more
+    # (the exact sums: multiples of 2^-30 in whole numbers, the rests below them in extended precision)
+    r = rho.cpu().numpy()
+    whole = np.floor(np.ldexp(r, 30))
+    want = np.ldexp(np.cumsum(whole.astype(np.int64)).astype(np.longdouble), -30)
+    want += np.cumsum((r - np.ldexp(whole, -30)).astype(np.longdouble))
     got = first.cpu().numpy()
     row = rho.reshape(-1, ngrid).sum(1).cpu().numpy().max()
     assert np.all(np.abs(got - want) <= 2.0 ** -53 * (2.0 * want + ngrid * row) * 1.01)
