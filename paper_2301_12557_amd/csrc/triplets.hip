@@ -437,8 +437,10 @@ __device__ inline void tri_pairs(const TriArgs& a, const BinTable& T, const floa
                 for (int i = 0; i < 4; i++) {
                     const int p = rb * 16 + 4 * g + i;
                     if (e[i] < -1) {
+                        // (the product form of a short side can come out below 0; its square
+                        // lies in every band that reaches 0 then, which 0 does too)
                         if (!EXACT)
-                            e[i] = tri_hot(T, nband, e[i], v[i] * a.inv_scale, [&] {
+                            e[i] = tri_hot(T, nband, e[i], fmaxf(v[i] * a.inv_scale, 0.0f), [&] {
                                 const float4 dp = P.d[p], dq = Q.d[q];
                                 const float ex = dq.x - dp.x, ey = dq.y - dp.y, ez = dq.z - dp.z;
                                 return __builtin_fmaf(ez, ez, __builtin_fmaf(ey, ey, ex * ex));

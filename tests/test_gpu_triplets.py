@@ -270,3 +270,31 @@ def test_lists_at_the_edges_of_blocks(m, nb, weighted):
     else:
         got, st = _gpu_tri(x, e, 60.0)
         assert_same(got, oracle.triplets(x, edges=e, box=60.0), what=f"clump {m}")
+
+
+@pytest.mark.parametrize("box", [130.0, 0.0])
+@pytest.mark.parametrize("edges", [[0.0, 0.002, 0.005, 0.01, 30.0], [0.004, 0.008, 0.1, 30.0]])
+@pytest.mark.parametrize("nb,weighted", [(0, False), (17, False), (0, True)])
+def test_very_short_sides(box, edges, nb, weighted):
+    """Neighbours 1e-3 to 1e-2 apart, up to 30 from the primary: the side's square
+    |p|^2 - 2 p.q + |q|^2 cancels to within its rounding and can come out below
+    0, and edges as short lie inside bands that reach 0."""
+    rng = np.random.default_rng(41)
+    x = rng.uniform(0, 120, (500, 3))
+    d = rng.normal(size=x.shape)
+    d *= (10.0 ** rng.uniform(-3, -2, len(x)) / np.linalg.norm(d, axis=1))[:, None]
+    x = np.concatenate([x, np.clip(x + d, 0, np.nextafter(120.0, 0))])
+    e = np.asarray(edges)
+    if nb:  # more bins: sorted counters
+        e = np.concatenate([e[:-1], np.linspace(1.0, 30.0, nb - len(e) + 2)])
+    note(f"triplets: short sides, {len(e) - 1} bins from {e[0]}, weighted {weighted}, box {box}")
+    if weighted:
+        w = rng.uniform(0.5, 2.0, len(x))
+        c, wc, _ = _gpu_tri_w(x, w, e, box)
+        rc, rw = oracle.triplets(x, edges=e, box=box, w=w)
+        assert_same(c, rc, wc, rw, what="short sides")
+    else:
+        got, _ = _gpu_tri(x, e, box)
+        ref = oracle.triplets(x, edges=e, box=box)
+        assert ref.sum() > 1e5 and ref[:-1].sum() > 1000
+        assert_same(got, ref, what="short sides")
