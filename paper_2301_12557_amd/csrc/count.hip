@@ -249,11 +249,13 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
                               (mid ? MIN_WAVE_LDS_MID : MIN_WAVE_LDS) + 64 <= maxlds;
     Lut1D s1, s2;
     if (accepted && !fits) {
-        FCFC_TRY(plan_short_tables(p, s1, s2));
         T1 = &s1;
         T2 = &s2;
-        shared_bytes = shared_for((int)T1->tab.size(), two ? (int)T2->tab.size() : 0);
-        fits = choose_waves(shared_bytes, waves, resident);
+        for (int lg = p->tab_log2 - 1; lg >= 0 && !fits; lg--) {
+            FCFC_TRY(plan_short_tables(p, lg, s1, s2));
+            shared_bytes = shared_for((int)T1->tab.size(), two ? (int)T2->tab.size() : 0);
+            fits = choose_waves(shared_bytes, waves, resident);
+        }
     } else if (p->has_big && !lin) {
         const int sb = shared_for((int)p->lut1b.tab.size(), two ? (int)p->lut2b.tab.size() : 0);
         int wb = 1, rb = 0;

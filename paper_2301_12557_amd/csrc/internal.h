@@ -121,7 +121,7 @@ struct Plan {
     // its relative rounding, which computed bins (uniform edges) allow for
     ErrModel em1;
     double e_pi = 0;
-    ErrModel tab1, tab2;        // error models and length of lut1 and lut2 (plan_short_tables)
+    ErrModel tab1, tab2;        // error models of lut1 and lut2, and their length (at most 2^tab_log2)
     int tab_log2 = 13;
     bool mu_top_closed = true;
     uint64_t id = 0;            // unique plan id (cells remember it)
@@ -186,8 +186,8 @@ fcfc_status plan_finalize_grid(Plan* p);
 fcfc_status plan_finalize_numerics(Plan* p);
 int choose_k(const Plan* p, int64_t n_hint);
 int stencil_rows(const Plan* p, bool half, std::vector<int4>& rows);
-// Tables of half the length of lut1 and lut2 with the same bands.
-fcfc_status plan_short_tables(const Plan* p, Lut1D& t1, Lut1D& t2);
+// Tables of at most 2^log2 entries with the bands of lut1 and lut2.
+fcfc_status plan_short_tables(const Plan* p, int log2, Lut1D& t1, Lut1D& t2);
 // Table over the first-axis squared edges for binning values given in FP64:
 // its bands cover only the rounding of a value to FP32, so it depends on the
 // edges alone (no grid); built on first use and kept by the plan.

@@ -259,9 +259,9 @@ fcfc_status plan_side_tables(Plan* p, double e_axis, double e_abs, int lg, const
     return FCFC_OK;
 }
 
-fcfc_status plan_short_tables(const Plan* p, Lut1D& t1, Lut1D& t2) {
-    FCFC_TRY(build_lut(t1, p->e1, p->tab1, p->tab_log2 - 1));
-    if (p->kind == FCFC_BIN_SPERP_PI) FCFC_TRY(build_lut(t2, p->e2, p->tab2, p->tab_log2 - 1));
+fcfc_status plan_short_tables(const Plan* p, int log2, Lut1D& t1, Lut1D& t2) {
+    FCFC_TRY(build_lut(t1, p->e1, p->tab1, log2));
+    if (p->kind == FCFC_BIN_SPERP_PI) FCFC_TRY(build_lut(t2, p->e2, p->tab2, log2));
     return FCFC_OK;
 }
 
@@ -289,10 +289,11 @@ fcfc_status plan_finalize_numerics(Plan* p) {
     p->has_big = false;
     p->lut1b = Lut1D();
     p->lut2b = Lut1D();
-    p->em1 = d2m;
+    p->em1 = p->tab1 = p->tab2 = d2m;
     p->e_pi = e;
+    p->tab_log2 = p->kind == FCFC_BIN_SPERP_PI ? std::max(8, lg - 1) : lg;
     if (p->kind == FCFC_BIN_S || p->kind == FCFC_BIN_S_MU) {
-        FCFC_TRY(build_lut(p->lut1, p->e1, d2m, lg));
+        FCFC_TRY(build_lut(p->lut1, p->e1, d2m, p->tab_log2));
         if (big) FCFC_TRY(build_lut(p->lut1b, p->e1, d2m, lg + 1));
         p->r2prune32 = p->lut1.vmax;
         p->lut2 = Lut1D();
@@ -344,8 +345,8 @@ fcfc_status plan_finalize_numerics(Plan* p) {
         // a computed bin squares |pi| = |dot| rsq(|l|^2), with twice the reciprocal's error
         if (p->los == FCFC_LOS_MIDPOINT)
             p->em1.B += 1.5 * (TRANS_REL + 6.0 * u) * (p->e2.back() * p->e2.back() * (1.0 + 1e-3) + 1.0);
-        FCFC_TRY(build_lut(p->lut1, p->e1, m1, std::max(8, lg - 1)));
-        FCFC_TRY(build_lut(p->lut2, p->e2, m2, std::max(8, lg - 1)));
+        FCFC_TRY(build_lut(p->lut1, p->e1, m1, p->tab_log2));
+        FCFC_TRY(build_lut(p->lut2, p->e2, m2, p->tab_log2));
         if (big) {
             FCFC_TRY(build_lut(p->lut1b, p->e1, m1, std::min(14, lg + 1)));
             FCFC_TRY(build_lut(p->lut2b, p->e2, m2, std::min(14, lg + 1)));

@@ -156,3 +156,25 @@ def test_pairs_along_and_across_the_line_of_sight(n2, los):
     for lo in (0.0, 1.0):
         check_case("mu ends", x, kind="smu", edges1=synth.linear_edges(lo, 6, 10), edges2=synth.mu_edges(n2), los=los,
                    box=50.0 if los == "z" else 0.0)
+
+
+@pytest.mark.parametrize("kind,n1,n2,tune", [("smu", 449, 20, {"hist_copies": 4}), ("smu", 361, 50, {"hist_copies": 2}),
+                                             ("smu", 123, 80, {"hist_copies": 4, "lut_log2": 10}),
+                                             ("spi", 229, 40, {"hist_copies": 4}),
+                                             ("spi", 196, 50, {"hist_copies": 4, "lut_log2": 10})])
+def test_tables_shortened_beside_large_histograms(kind, n1, n2, tune):
+    """Accepted histograms beside which the default tables do not leave room for a
+    wave: shorter tables with the same bands, exact counts; a third of the points
+    have a partner within FP32 rounding of an edge."""
+    rng = np.random.default_rng(n1)
+    x = rng.random((2000, 3)) * 50.0
+    e1 = synth.log_edges(0.1, 20.0, n1)
+    e2 = synth.mu_edges(n2) if kind == "smu" else np.linspace(0, 10, n2 + 1) ** 1.1
+    y = x[:1000].copy()
+    y[:, 0] = np.mod(y[:, 0] + rng.choice(e1, 1000) * (1 + rng.uniform(-1, 1, 1000) * 2e-7), 50.0)
+    x = np.concatenate([x, y])
+    plan = fcfc.Plan(kind, e1, e2, box=50.0, n_hint=len(x), **tune)
+    full = len(plan.table(0)["tab"])
+    plan.close()
+    _, _, st = check_case("short tables", x, kind=kind, edges1=e1, edges2=e2, los="z", box=50.0, **tune)
+    assert 0 < st["lut_entries"] <= full // 2 + 1
