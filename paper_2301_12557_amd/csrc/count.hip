@@ -699,7 +699,8 @@ fcfc_status count_pairs(Plan* p, Cells* c1, Cells* c2, int64_t* d_counts, double
                            items2);
         run_items = items2;
     }
-    uint32_t* times = p->tune.record_timing ? (uint32_t*)(scr2 + 2 * s_items + 4 * s_sort + s_rs) : nullptr;
+    // (none in a caller's workspace: no room is reserved for them there)
+    uint32_t* times = s_times ? (uint32_t*)(scr2 + 2 * s_items + 4 * s_sort + s_rs) : nullptr;
 
     a.posA = c1->pos32;
     a.absA = c1->abs32;

@@ -136,3 +136,22 @@ def test_noalloc_long_list_is_cut_coarser(n, b_chunk, rc):
         assert out.cpu().tolist() == [-3] * 4
     c.close()
     plan.close()
+
+
+def test_noalloc_records_no_timings():
+    """record_timing = 1: the counts are those of the allocating call, and the plan
+    keeps no item times (the scratch array has no room for them)."""
+    from paper_2301_12557_amd import fcfc
+    lib = fcfc.load()
+    plan = fcfc.Plan("smu", synth.linear_edges(0, 100, 10), synth.mu_edges(10), box=1000.0, n_hint=5000,
+                     record_timing=1)
+    c = plan.build_cells(to_dev(synth.uniform_box(5000, 1000.0, 11)))
+    note("noalloc with record_timing")
+    got, _ = _counts(lib, "fcfc_count_pairs_noalloc", plan, c, None, 100, False)
+    n = ctypes.c_int64(0)
+    assert lib.fcfc_plan_timings(plan.h, None, None, 0, ctypes.byref(n), None) == -10
+    ref, _ = _counts(lib, "fcfc_count_pairs", plan, c, None, 100, False)
+    assert np.array_equal(got, ref)
+    assert lib.fcfc_plan_timings(plan.h, None, None, 0, ctypes.byref(n), None) == 0 and n.value > 0
+    c.close()
+    plan.close()
