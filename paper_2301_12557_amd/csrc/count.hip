@@ -615,7 +615,7 @@ fcfc_status count_pairs(Plan* p, Cells* c1, Cells* c2, int64_t* d_counts, double
         s_pred = model ? al256((size_t)std::max<uint32_t>(nitems, 1) * 20) : 0;
         s2 = 2 * s_items + 4 * s_sort + s_rs + s_times + s_pred;
         // a list too long for the caller's workspace is cut into longer items
-        if (!ws || s1 + s2 <= ws->bytes || tree || p->tune.b_chunk || L.bchunk == BCHUNK_LONG) break;
+        if (!ws || s1 + s2 <= ws->bytes || p->tune.b_chunk || L.bchunk == BCHUNK_LONG) break;
         L.bchunk = w.bchunk = BCHUNK_LONG;
     }
     char* scr2 = nullptr;

@@ -155,3 +155,29 @@ def test_noalloc_records_no_timings():
     assert lib.fcfc_plan_timings(plan.h, None, None, 0, ctypes.byref(n), None) == 0 and n.value > 0
     c.close()
     plan.close()
+
+
+@pytest.mark.parametrize("b_chunk,rc", [(0, 0), (2048, -5)])
+def test_noalloc_long_tree_list_is_cut_coarser(b_chunk, rc):
+    """The same for a tree: the ranges of leaves wholly in reach merge to lengths of
+    10^5 points, in some 900,000 items of the default length."""
+    import torch
+    from paper_2301_12557_amd import fcfc
+    lib = fcfc.load()
+    n = 700000
+    plan = fcfc.Plan("s", synth.linear_edges(0, 100, 4), n_hint=n, tree_leaf=128, b_chunk=b_chunk)
+    plan.set_bounds((0.0,) * 3, (100.0,) * 3)
+    c = plan.build_cells(to_dev(synth.uniform_box(n, 50.0, 9) + 20.0))
+    note(f"noalloc long tree list b_chunk={b_chunk}")
+    out = torch.full((4,), -3, dtype=torch.int64, device="cuda")
+    assert lib.fcfc_count_pairs_noalloc(plan.h, c.h, None, ctypes.c_void_p(out.data_ptr()), None,
+                                        ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == rc
+    torch.cuda.synchronize()
+    if rc == 0:
+        ref, _ = _counts(lib, "fcfc_count_pairs", plan, c, None, 4, False)
+        assert np.array_equal(out.cpu().numpy(), ref)
+        assert int(ref.sum()) == n * (n - 1) // 2
+    else:
+        assert out.cpu().tolist() == [-3] * 4
+    c.close()
+    plan.close()
