@@ -618,6 +618,7 @@ fcfc_status count_pairs(Plan* p, Cells* c1, Cells* c2, int64_t* d_counts, double
         if (!ws || s1 + s2 <= ws->bytes || p->tune.b_chunk || L.bchunk == BCHUNK_LONG) break;
         L.bchunk = w.bchunk = BCHUNK_LONG;
     }
+    p->last_scratch = s1 + s2;
     char* scr2 = nullptr;
     if (ws) {
         // s1 is a sum of 256-byte multiples, so the second part stays aligned

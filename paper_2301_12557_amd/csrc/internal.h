@@ -133,6 +133,7 @@ struct Plan {
     bool have_stats = false;
     int64_t* last_counts = nullptr;  // device histogram of the last count (for stats)
     int64_t last_counts_n = 0;       // its entries when not nbins (triangle counts)
+    size_t last_scratch = 0;         // scratch of the last count, bytes
     void* timing_dev = nullptr;      // last recorded per-item times (u32) followed by the items
     uint32_t timing_n = 0;
     std::vector<char> host_stage;    // host copies of uploaded tables / kernel arguments

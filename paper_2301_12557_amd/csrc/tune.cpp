@@ -32,9 +32,10 @@ struct Ctx {
 };
 
 // GPU time (ms) of build + count under tuning t: the best of `reps` runs
-// (the model is attached when t asks for the learned order).
+// (the model is attached when t asks for the learned order), and the scratch
+// the count takes.
 // Returns FCFC_ERANGE (and leaves *ms alone) where the tuning is not possible.
-fcfc_status time_config(Ctx& c, const fcfc_tuning& t, int reps, double* ms) {
+fcfc_status time_config(Ctx& c, const fcfc_tuning& t, int reps, double* ms, size_t* scratch) {
     fcfc_plan_t pl = nullptr;
     FCFC_TRY(fcfc_plan_create(c.kind, c.los, c.e1, c.n1, c.e2, c.n2, c.L, &t, &pl));
     fcfc_status s = FCFC_OK;
@@ -58,6 +59,7 @@ fcfc_status time_config(Ctx& c, const fcfc_tuning& t, int reps, double* ms) {
         fcfc_cells_free(a);
         fcfc_cells_free(b);
     }
+    *scratch = ((const Plan*)pl)->last_scratch;
     fcfc_plan_free(pl);
     if (s == FCFC_OK) *ms = best;
     return s;
@@ -202,13 +204,17 @@ extern "C" fcfc_status fcfc_autotune(fcfc_model_t model, int32_t kind, int32_t l
     auto consider = [&](const fcfc_tuning& t) -> double {
         if (s != FCFC_OK) return INFINITY;
         double ms = INFINITY;
-        fcfc_status r = time_config(c, t, 2, &ms);
+        size_t scratch = 0;
+        fcfc_status r = time_config(c, t, 2, &ms, &scratch);
         ntried++;
         if (r == FCFC_ERANGE) return INFINITY;  // not possible (grid, LDS): skip
         if (r != FCFC_OK) {
             s = r;
             return INFINITY;
         }
+        // Shorter items than the base asks for must leave the no-alloc count
+        // possible, which keeps a b_chunk that is set.
+        if (r == FCFC_OK && t.b_chunk != t0.b_chunk && (int64_t)scratch > fcfc_noalloc_scratch_bytes()) return INFINITY;
         if (ms < bms) {
             bms = ms;
             bt = t;

@@ -137,3 +137,29 @@ def test_tuning_gain_on_clustered_catalogue(blobs):
     assert n1 >= n0
     assert analytic >= 1.25 * tuned
     assert tuned <= 1.10 * free
+
+
+def test_tuned_list_fits_the_no_alloc_scratch():
+    """A tuning that may set shorter work items still runs through the no-alloc entry
+    point where the default's list of this catalogue fits (some 10^6 items of 512
+    points do not)."""
+    import ctypes
+
+    import torch
+    from paper_2301_12557_amd import fcfc
+    lib = fcfc.load()
+    dx = to_dev(_blobs(1_000_000, 10, 5.0, 0.9, 9))
+    t, best, heur, n = fcfc.autotune(dx, kind="smu", edges1=E1, edges2=E2, box=L)
+    note(f"tuned {t} {best:.3f} ms (analytic {heur:.3f}) trials {n}")
+    counts = []
+    for kw in (dict(n_hint=len(dx)), _plan_kw(t)):
+        plan = fcfc.Plan("smu", E1, E2, box=L, **kw)
+        c = plan.build_cells(dx)
+        out = torch.zeros(200, dtype=torch.int64, device="cuda")
+        assert lib.fcfc_count_pairs_noalloc(plan.h, c.h, None, ctypes.c_void_p(out.data_ptr()), None,
+                                            ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+        torch.cuda.synchronize()
+        counts.append(out)
+        c.close()
+        plan.close()
+    assert torch.equal(*counts)
