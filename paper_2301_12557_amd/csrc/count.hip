@@ -74,13 +74,18 @@ static int tile_seg(const Plan* p) { return p->tune.seg_cells > 0 ? std::min(32,
 // centred on the A points, each coordinate within a few u (2^-24) times the
 // extent W of the pair's surroundings, and on |a|^2 - 2 a.b + |b|^2, whose
 // terms are below W^2: the error stays below some 70 u W^2, and the margin
-// taken is 128 u W^2 (and 64 u W on the second axis).  Only pairs truly in
-// range have to pass: bin_queue decides.
+// taken is 128 u W^2 (and 64 u W on the second axis).  The coordinates of a
+// tree are rounded relative to their leaf's origin, which may lie at a distance
+// X far beyond W (a few points along a beam fill one leaf): each component is
+// off by another 3 u X at most, the square by 10.4 u X W, and the margins are
+// 128 u W (W + X) and 64 u (W + X).  Only pairs truly in range have to pass:
+// bin_queue decides.
 static void set_filter(const Plan* p, CountArgs& a) {
     const double u = 5.9604644775390625e-08;
     const double up = 1.0 + 1e-6;
     const double e1 = p->e1.back();
     a.f_reach = (float)(p->rprune * up);
+    a.f_ext = p->tune.tree_leaf > 0 ? (float)(p->tree_side * up) : 0.f;
     a.f_slack = (float)(128.0 * u);
     a.f_uslack = (float)(64.0 * u);
     double t2 = e1 * e1, cull2 = e1 * e1, ul = 0.0, er = 0.0;

@@ -117,6 +117,7 @@ struct CountArgs {
     // for (s_perp, pi)), squared reach from the box of the A points, second
     // axis, and the margins
     float f_t2, f_cull2, f_u, f_reach, f_slack, f_uslack, f_uerr, f_ts;
+    float f_ext;  // tree: largest leaf-local coordinate
     // uniform edges: x = s l1c + l1o (and |pi| l2c + l2o) is the bin plus a
     // fraction, good to l1a / s + l1t (l2t)
     int lin;
@@ -932,12 +933,14 @@ void k_count(const CountArgs* argp) {
         const float cy = uniform_f(0.5f * (y0 + y1)), hy = uniform_f(y1 - cy);
         const float cz = uniform_f(0.5f * (z0 + z1)), hz = uniform_f(z1 - cz);
         // thresholds with the margin of the frame's FP32 errors: the squared
-        // separation of points within W = 2 |half box| + reach of each other
+        // separation of points within W = 2 |half box| + reach of each other, and
+        // for trees the rounding of coordinates up to f_ext from their leaf's origin
         const float wsum = 2.0f * (hx + hy + hz) + 4.0f * k.side32 + a.f_reach;
-        const float slack = a.f_slack * wsum * wsum;
+        const float wext = TREE ? wsum + a.f_ext : wsum;
+        const float slack = a.f_slack * wsum * wext;
         float t2 = a.f_t2 + slack;  // squared separation (transverse part for (s_perp, pi))
         const float cull2 = uniform_f(a.f_cull2 + slack);
-        float ulim = a.f_u + a.f_uslack * wsum;
+        float ulim = a.f_u + a.f_uslack * wext;
         if (LIN) {
             // Positions in the frame of the tile's first cell: over S = (x1 - x0) /
             // side + 1 cells the roundings of one displacement component come to

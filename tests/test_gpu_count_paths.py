@@ -178,3 +178,27 @@ def test_tables_shortened_beside_large_histograms(kind, n1, n2, tune):
     plan.close()
     _, _, st = check_case("short tables", x, kind=kind, edges1=e1, edges2=e2, los="z", box=50.0, **tune)
     assert 0 < st["lut_entries"] <= full // 2 + 1
+
+
+@pytest.mark.parametrize("axis", [0, 2])
+@pytest.mark.parametrize("kind,los", [("s", "z"), ("smu", "z"), ("smu", "mid"), ("spi", "mid"), ("spi", "z")])
+def test_tree_leaves_much_longer_than_the_reach(kind, los, axis):
+    """Close pairs between tight clumps and a few points along a pencil beam, one leaf
+    thousands of reaches long: the rounding of its leaf-local coordinates is what the
+    candidate filter has to allow for.  The partners lie along the beam, within 1e-3 to
+    1e-7 of the outer edge."""
+    rng = np.random.default_rng(7)
+    r = 0.3
+    size = np.full(3, 4.0)
+    size[axis] = 2000.0
+    cen = 300.0 + rng.random((20, 3)) * size
+    x = np.repeat(cen, 600, axis=0) + rng.uniform(-0.1, 0.1, (12000, 3)) * r
+    y = x[::100].copy()
+    reach = 0.8 * r if kind == "spi" and axis == 2 else r
+    y[:, axis] += reach * (1.0 - 10.0 ** rng.uniform(-7, -3, len(y))) * rng.choice([-1.0, 1.0], len(y))
+    for p in (1.0, 1.2):
+        e1 = r * np.linspace(0.0, 1.0, 10) ** p
+        e2 = synth.mu_edges(7) if kind == "smu" else 0.8 * r * np.linspace(0.0, 1.0, 6) ** p if kind == "spi" else None
+        kw = dict(kind=kind, edges1=e1, edges2=e2, los=los, box=0.0, tree_leaf=128)
+        check_case("beam", x, y, **kw)
+        check_case("beam, the other way", y, x, **kw)
