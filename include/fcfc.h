@@ -142,8 +142,10 @@ typedef struct {
  *            pi edges for SPERP_PI; NULL and n2 = 0 for S.
  *   box_L    > 0: periodic cube [0,L)^3 (needs prune radius <= L/2); 0: open box.
  *   tune     NULL or knobs.
- * Errors: FCFC_EINVAL, FCFC_EEDGES, FCFC_ERANGE (prune radius > L/2, or the
- * histogram does not fit in LDS), FCFC_ENOMEM.  Host only; no GPU work.
+ * Errors: FCFC_EINVAL, FCFC_EEDGES, FCFC_ERANGE (prune radius > L/2, the
+ * histogram does not fit in LDS, or the square of the largest edge of an axis is
+ * no normal FP32 number: largest edges below 1.1e-19 or above 1.8e19; open boxes
+ * report that when their bounds are set), FCFC_ENOMEM.  Host only; no GPU work.
  */
 fcfc_status fcfc_plan_create(int32_t kind, int32_t los, const double *edges1, int32_t n1,
                              const double *edges2, int32_t n2, double box_L,

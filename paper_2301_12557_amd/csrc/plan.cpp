@@ -195,8 +195,14 @@ static fcfc_status build_lut(Lut1D& t, const std::vector<double>& edges, const E
     // scale: a power of two giving at most 2^log2_target entries
     double target = ldexp(1.0, log2_target);
     int e;
+    if (!(t.vmax >= FLT_MIN && t.vmax <= FLT_MAX)) {
+        set_error("the square of the largest edge %.3g leaves the FP32 range", edges.back());
+        return FCFC_ERANGE;
+    }
     frexp(target / (double)t.vmax, &e);  // target/vmax = f * 2^e, f in [0.5,1)
-    double scale = ldexp(1.0, e - 1);     // <= target / vmax
+    // <= target / vmax, and finite in FP32 (an index formed with an infinite
+    // scale would leave the table)
+    double scale = ldexp(1.0, std::min(e - 1, 127));
     t.scale = (float)scale;
     int64_t nt = (int64_t)ceil((double)t.vmax * scale) + 1;
     if (nt > 32767) nt = 32767;  // cannot happen with log2_target <= 14

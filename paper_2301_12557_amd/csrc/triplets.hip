@@ -395,12 +395,12 @@ __device__ inline void tri_pairs(const TriArgs& a, const BinTable& T, const floa
     typedef float f4 __attribute__((ext_vector_type(4)));
     nside += SELF ? (unsigned long long)(mp * (mp - 1) / 2) : (unsigned long long)mp * (unsigned long long)mq;
     const int g = lane >> 4, c = lane & 15;
-    const float mul = g == 3 ? T.scale : -2.0f * T.scale;
+    const float mul = g == 3 ? 1.0f : -2.0f;
     const uint32_t nb = (uint32_t)T.nb, nb2 = nb * nb;
     const uint32_t hist_l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned long long*)hist;
     const int np = (mp + 15) >> 4, nq = (mq + 15) >> 4;
     for (int rb = 0; rb < np; rb++) {
-        const float A = ((const float*)P.d)[(rb * 16 + c) * 4 + g] * mul;
+        const float A = ((const float*)P.d)[(rb * 16 + c) * 4 + g] * T.scale * mul;
         const uint32_t pb4 = ((const uint32_t*)P.bin)[rb * 4 + g];
         uint32_t pb[4];
 #pragma unroll

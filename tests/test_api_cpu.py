@@ -393,3 +393,27 @@ def test_tree_plan_validation():
     p.set_bounds([500.0, 0.0, -100.0], [900.0, 400.0, 100.0])
     assert p.numerics()["nx"] > 0
     p.close()
+
+
+@pytest.mark.parametrize("kind", [0, 1, 2])
+def test_edges_whose_squares_leave_fp32(kind):
+    """Largest edges from 1e-19 to 1.8e19 are taken, with finite table scales and
+    every index inside the table; beyond that their squares are no FP32 numbers
+    (an infinite top or a top of zero), and the plan is refused."""
+    for r, ok in ((1e-170, 0), (1e-23, 0), (2e-19, 1), (1e-17, 1), (3e-17, 1), (1e-10, 1), (1e10, 1), (1.7e19, 1),
+                  (2e19, 0), (1e25, 0), (1e160, 0)):
+        e1 = np.linspace(0, 1, 9) ** 1.1 * r
+        e2 = None if kind == 0 else np.arange(6) / 5.0 if kind == 1 else np.linspace(0, 1.0, 4) * r
+        # (where the squares leave FP64 too, -6 or -5 as before)
+        assert _create(kind=kind, e1=e1, e2=e2, L=4 * r) in ((0,) if ok else (-5, -6) if r > 1e150 else (-5,)), r
+        if not ok:
+            continue
+        p = fcfc.Plan(("s", "smu", "spi")[kind], e1, e2, box=4 * r, n_hint=1000)
+        for which in range(4 if kind == 2 else 3):
+            if which == 1 and kind != 2:
+                continue
+            t = p.table(which)
+            assert 0 < t["scale"] < np.inf and 0 < t["vmax"] < np.inf
+            below = float(np.nextafter(t["vmax"], np.float32(0)))
+            assert np.floor(below * float(t["scale"])) < len(t["tab"])
+        p.close()
