@@ -405,7 +405,7 @@ def test_edges_whose_squares_leave_fp32(kind):
         e1 = np.linspace(0, 1, 9) ** 1.1 * r
         e2 = None if kind == 0 else np.arange(6) / 5.0 if kind == 1 else np.linspace(0, 1.0, 4) * r
         # (where the squares leave FP64 too, -6 or -5 as before)
-        assert _create(kind=kind, e1=e1, e2=e2, L=4 * r) in ((0,) if ok else (-5, -6) if r > 1e150 else (-5,)), r
+        assert _create(kind=kind, e1=e1, e2=e2, L=4 * r) in ((0,) if ok else (-5,) if 1e-150 < r < 1e150 else (-5, -6)), r
         if not ok:
             continue
         p = fcfc.Plan(("s", "smu", "spi")[kind], e1, e2, box=4 * r, n_hint=1000)
