@@ -83,6 +83,12 @@ static int tile_seg(const Plan* p) { return p->tune.seg_cells > 0 ? std::min(32,
 static void set_filter(const Plan* p, CountArgs& a) {
     const double u = 5.9604644775390625e-08;
     const double up = 1.0 + 1e-6;
+    // the reach is 16 to 32 units (as far as a unit's square is a normal FP32 number)
+    const int e = std::min(std::max(ilogb(p->rprune) - 4, -62), 59);
+    const double sig = ldexp(1.0, -e), sig2 = sig * sig;
+    a.f_sig = (float)sig;
+    a.f_inv = (float)(1.0 / sig);
+    a.f_inv2 = (float)(1.0 / sig2);
     const double e1 = p->e1.back();
     a.f_reach = (float)(p->rprune * up);
     a.f_ext = p->tune.tree_leaf > 0 ? (float)(p->tree_side * up) : 0.f;
@@ -96,11 +102,11 @@ static void set_filter(const Plan* p, CountArgs& a) {
             er = 64.0 * u * sqrt(3.0) * p->coord_max;  // distances from the observer
         }
     }
-    a.f_t2 = (float)(t2 * up);
-    a.f_cull2 = (float)(cull2 * up);
-    a.f_u = (float)(ul * up);
-    a.f_uerr = (float)(er * up);
-    a.f_ts = (float)(4.0 * ul * er * up);
+    a.f_t2 = (float)(t2 * up * sig2);
+    a.f_cull2 = (float)(cull2 * up * sig2);
+    a.f_u = (float)(ul * up * sig);
+    a.f_uerr = (float)(er * up * sig);
+    a.f_ts = (float)(4.0 * ul * er * up * sig2);
 }
 
 // Uniform edges on every axis: the constants of the computed bins.  The

@@ -118,6 +118,7 @@ struct CountArgs {
     // axis, and the margins
     float f_t2, f_cull2, f_u, f_reach, f_slack, f_uslack, f_uerr, f_ts;
     float f_ext;  // tree: largest leaf-local coordinate
+    float f_sig, f_inv, f_inv2;  // the filter's unit: a power of two, its inverse and that squared
     // uniform edges: x = s l1c + l1o (and |pi| l2c + l2o) is the bin plus a
     // fraction, good to l1a / s + l1t (l2t)
     int lin;
@@ -870,6 +871,8 @@ void k_count(const CountArgs* argp) {
     // mock of 200,003 points 1.76 -> 1.14 ms, 10M points in 50 log bins 3.97 ->
     // 2.95 ms, 1M weighted points 6.36 -> 5.01 ms, 200k x 4M weighted survey (mid
     // point) 119 -> 80 ms, tree survey 7.65 -> 4.49 ms.
+    // All of this works in units of a power of two near the reach (CountArgs.f_sig),
+    // so that no square or sentinel leaves FP32 whatever unit the coordinates have.
     // (s_perp, pi) counts also bound the second axis: dz for the z line of
     // sight; for the mid-point one, the difference of the two distances
     // dr = |b| - |a| from the observer.  With
@@ -937,10 +940,13 @@ void k_count(const CountArgs* argp) {
         // for trees the rounding of coordinates up to f_ext from their leaf's origin
         const float wsum = 2.0f * (hx + hy + hz) + 4.0f * k.side32 + a.f_reach;
         const float wext = TREE ? wsum + a.f_ext : wsum;
-        const float slack = a.f_slack * wsum * wext;
+        const float sig = a.f_sig;  // (from here on thresholds are in the filter's unit)
+        const float slack = a.f_slack * (sig * wsum) * (sig * wext);
         float t2 = a.f_t2 + slack;  // squared separation (transverse part for (s_perp, pi))
-        const float cull2 = uniform_f(a.f_cull2 + slack);
-        float ulim = a.f_u + a.f_uslack * wext;
+        const float c2 = a.f_cull2 + slack;
+        const float cull2 = uniform_f(c2 * a.f_inv2);
+        float ulim = a.f_u + a.f_uslack * (sig * wext);
+        const float ucull = uniform_f(ulim * a.f_inv);
         if (LIN) {
             // Positions in the frame of the tile's first cell: over S = (x1 - x0) /
             // side + 1 cells the roundings of one displacement component come to
@@ -960,15 +966,16 @@ void k_count(const CountArgs* argp) {
                 if (MID) c.t1a = k.l1a * widen;
             }
         }
-        const float X = av_ok ? fx - cx : far, Y = av_ok ? av.y - cy : far, Z = av_ok ? av.z - cz : far;
+        const float X = av_ok ? sig * (fx - cx) : far, Y = av_ok ? sig * (av.y - cy) : far,
+                    Z = av_ok ? sig * (av.z - cz) : far;
         // second coordinate u: z, or the distance from the observer
         float Fx = 0.f, Fy = 0.f, Fz = 0.f, ua = 0.f, ulo = 0.f, uhi = 0.f, uon = 1.f;
         if (SPI && MID) {
-            Fx = uniform_f(aabs.x - (fx - cx));  // the frame's origin as seen by the observer
-            Fy = uniform_f(aabs.y - (av.y - cy));
-            Fz = uniform_f(aabs.z - (av.z - cz));
-            ua = __builtin_amdgcn_sqrtf(
-                __builtin_fmaf(aabs.z, aabs.z, __builtin_fmaf(aabs.y, aabs.y, aabs.x * aabs.x)));
+            Fx = uniform_f(sig * (aabs.x - (fx - cx)));  // the frame's origin as seen by the observer
+            Fy = uniform_f(sig * (aabs.y - (av.y - cy)));
+            Fz = uniform_f(sig * (aabs.z - (av.z - cz)));
+            const float ax = sig * aabs.x, ay = sig * aabs.y, az = sig * aabs.z;
+            ua = __builtin_amdgcn_sqrtf(__builtin_fmaf(az, az, __builtin_fmaf(ay, ay, ax * ax)));
             // |a| + |b| of a pair in range is at least smin; where it does not exceed
             // the reach twice over, the sphere alone filters (u = 0 for every point)
             const float umin = wave_min_f(ua), umax = wave_max_f(ua);
@@ -979,7 +986,7 @@ void k_count(const CountArgs* argp) {
                 ulim += a.f_uerr;
             } else {
                 uon = 0.f;
-                t2 = cull2;
+                t2 = c2;
                 ulim = 1.0f;
             }
             ulo = uon * umin - ulim;
@@ -1015,7 +1022,7 @@ void k_count(const CountArgs* argp) {
         // this lane's component of a staged B point in the A frame: the stored
         // component, plus the cell for x, plus an offset
         const float selside = (!TREE && !LIN && lk == 0) ? k.side32 : 0.f;
-        const float off_k = lk == 0 ? -cx : (lk == 1 ? (TREE ? 0.f : Dy) - cy : (TREE ? 0.f : Dz) - cz);
+        const float off_k = sig * (lk == 0 ? -cx : (lk == 1 ? (TREE ? 0.f : Dy) - cy : (TREE ? 0.f : Dz) - cz));
         const float F_k = lk == 0 ? Fx : (lk == 1 ? Fy : Fz);
         int ns = 0;  // staged B points waiting
         for (;;) {
@@ -1053,12 +1060,13 @@ void k_count(const CountArgs* argp) {
                         uz = fmaxf(fabsf(bz) - hz, 0.f);
             bool keep = j < b_end;
             if (SPI && !MID) {
-                keep = keep & (__builtin_fmaf(uy, uy, ux * ux) < cull2) & (uz < ulim);
+                keep = keep & (__builtin_fmaf(uy, uy, ux * ux) < cull2) & (uz < ucull);
             } else {
                 keep = keep & (__builtin_fmaf(uz, uz, __builtin_fmaf(uy, uy, ux * ux)) < cull2);
             }
             if (SPI && MID) {
-                const float px = bx + Fx, py = by + Fy, pz = bz + Fz;
+                const float px = __builtin_fmaf(bx, sig, Fx), py = __builtin_fmaf(by, sig, Fy),
+                            pz = __builtin_fmaf(bz, sig, Fz);
                 const float ub = uon * __builtin_amdgcn_sqrtf(
                                            __builtin_fmaf(pz, pz, __builtin_fmaf(py, py, px * px)));
                 keep = keep & (ub > ulo) & (ub < uhi);
@@ -1103,7 +1111,8 @@ void k_count(const CountArgs* argp) {
                 const uint32_t sat = s.wbase + OFF_SB + 16u * (uint32_t)slot;
                 float v = lds_f1(sat + 4u * (uint32_t)lk);
                 const uint32_t w = __float_as_uint(lds_f1(sat + 12u));
-                v = TREE || LIN ? v + off_k : __builtin_fmaf((float)(w & 255u) - 64.0f, selside, v) + off_k;
+                if (!TREE && !LIN) v = __builtin_fmaf((float)(w & 255u) - 64.0f, selside, v);
+                v = __builtin_fmaf(v, sig, off_k);
                 // slots past the last staged point (stale memory) become the origin with
                 // a |b|^2 out of every reach
                 const bool staged = slot < ns;

@@ -202,3 +202,26 @@ def test_tree_leaves_much_longer_than_the_reach(kind, los, axis):
         kw = dict(kind=kind, edges1=e1, edges2=e2, los=los, box=0.0, tree_leaf=128)
         check_case("beam", x, y, **kw)
         check_case("beam, the other way", y, x, **kw)
+
+
+@pytest.mark.parametrize("p", [-56, -50, -30, -16, 20, 30, 50, 54, 56, 58, 60])
+@pytest.mark.parametrize("kind,los,periodic", KINDS)
+def test_units_of_any_size(kind, los, periodic, p):
+    """The same catalogue in units from 2^-56 to 2^60: the filter's squares, the values
+    that mark unused lanes, and its margins hold at each.  (The mid-point line of sight
+    takes no box nearer to the observer than 1e-3, and needs |a + b|^2, for the tables of
+    (s_perp, pi) the square of its product with the separation, in FP32.)"""
+    if los == "mid" and not -17 < p < (24 if kind == "spi" else 54):
+        pytest.skip("outside the range of the mid-point line of sight")
+    rng = np.random.default_rng(8)
+    off = 0.0 if periodic else 300.0
+    x1, x2 = rng.random((150, 3)) * 40.0 + off, rng.random((333, 3)) * 40.0 + off
+    f = 2.0 ** p
+    for uniform in (True, False):
+        e1, e2 = _edges(kind, 14.0, uniform)
+        kw = dict(kind=kind, edges1=e1 * f, edges2=e2 * f if kind == "spi" else e2, los=los, box=40.0 * f if periodic else 0.0)
+        for k in (1, 3):
+            check_case("units", x1 * f, x2 * f, cells_per_rmax=k, **kw)
+        check_case("units, auto", x2 * f, **kw)
+        if not periodic:
+            check_case("units, tree", x1 * f, x2 * f, tree_leaf=32, **kw)
