@@ -20,8 +20,8 @@ def _check_sum(rho, ngrid, repeats):
     for _ in range(repeats):
         assert torch.equal(synth._running_sum_torch(rho, ngrid), first)
     # a row of ngrid adds up its values with at most ngrid roundings of the row's own
-    # sum; the sum of the rows before it is exact but for one rounding, and the
-    # addition of the two rounds once more
+    # sum; the sum of the rows before it adds one rounding (those of their own sums
+    # are far below it), and the addition of the two rounds once more
     # (the exact sums: multiples of 2^-30 in whole numbers, the rests below them in extended precision)
     r = rho.cpu().numpy()
     whole = np.floor(np.ldexp(r, 30))
