@@ -139,6 +139,7 @@ static void set_linear(const Plan* p, CountArgs& a) {
     const double abs1 = M * (p->em1.A + p->em1.C * s1) / 2.0 + (tr + 4.0 * u) * s1;
     a.l1t = (float)(1.01 * (abs1 + of1) / ds1 + 8.0 * u * (p->n1 + 1.0 + fabs(o1)));
     a.l1a = (float)(1.01 * p->em1.B / ds1);
+    a.zero2 = two && p->e2[0] == 0.0;
     if (two) {
         const double o2 = 1.0 - p->e2[0] / ds2, p2 = p->e2.back() * 1.01;
         a.l2c = (float)(1.0 / ds2);

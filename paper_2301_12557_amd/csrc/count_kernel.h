@@ -123,6 +123,7 @@ struct CountArgs {
     // fraction, good to l1a / s + l1t (l2t)
     int lin;
     float l1c, l1o, l1a, l1t, l2c, l2o, l2t;
+    int zero2;  // the second axis starts at 0
     float e_unit;  // u over the error of one displacement component
     float xstep;   // a row's points are sorted by x to this
     float mu_n, mu_c, tolA, tolC;  // mu_c: mu_n less mu_shrink
@@ -321,12 +322,13 @@ struct KConst {
     float scale1, scale2, vmax1, vmax2, mu_n, mu_nm1, tolA, tolC, side32;
     int lin;
     float l1c, l1o, l1a, l1t, l2c, l2o, l2t;  // uniform edges (CountArgs)
+    int zero2;
     float tolC_v;  // tolC held in a vector register (an fma takes one scalar operand)
     int n1, n2, nbins, nx, copies;
     WeightFmt wf;
 };
 
-// largest integer at or below x (0 for a NaN) in one instruction
+// largest integer at or below x (any integer for a NaN) in one instruction
 __device__ inline int floor_i(float x) {
     int r;
     __asm__("v_cvt_flr_i32_f32 %0, %1" : "=v"(r) : "v"(x));
@@ -497,8 +499,10 @@ __device__ __attribute__((always_inline)) inline void bin_queue(ArgsRef a, const
         lsq = __builtin_fmaf(lz, lz, __builtin_fmaf(ly, ly, lx * lx));
     }
     int b2 = 0;           // second bin
+    float b2f = 0.f;      // computed bins: with its fraction
     uint64_t near2 = 0;   // pairs near an edge of the second axis
     uint64_t in2 = ~0ull; // pairs in range of the second axis
+    uint64_t sure = 0;    // pairs in range and near no edge of the first axis
     float v1 = d2, rs = 0.f;  // first axis: squared separation, and its reciprocal square root
     if (KIND == FCFC_BIN_S_MU) {
         const float proj_n = MID ? fabsf(dot) * (__builtin_amdgcn_rsqf(lsq) * k.mu_n) : fabsf(dz) * k.mu_n;
@@ -523,9 +527,9 @@ __device__ __attribute__((always_inline)) inline void bin_queue(ArgsRef a, const
                 p = fabsf(dz);
                 v1 = __builtin_fmaf(dy, dy, dx * dx);
             }
-            const float x2 = __builtin_fmaf(p, k.l2c, k.l2o);
-            b2 = floor_i(x2);
-            near2 = __builtin_amdgcn_ballot_w64(!(fabsf(x2 - rintf(x2)) >= c.t2));
+            b2f = __builtin_fmaf(p, k.l2c, k.l2o);
+            b2 = floor_i(b2f);
+            near2 = __builtin_amdgcn_ballot_w64(!(fabsf(b2f - rintf(b2f)) >= c.t2));
             in2 = __builtin_amdgcn_ballot_w64((uint32_t)b2 < (uint32_t)k.n2);
         }
         if (KIND != FCFC_BIN_S_MU) rs = __builtin_amdgcn_rsqf(v1);
@@ -536,7 +540,9 @@ __device__ __attribute__((always_inline)) inline void bin_queue(ArgsRef a, const
         const float tol1 = SPI && MID ? __builtin_fmaf(c.t1a, rs, c.t1) : c.t1;
         const uint64_t near1 = __builtin_amdgcn_ballot_w64(!(fabsf(x1 - rintf(x1)) >= tol1));
         rm = (near1 | near2) & vmask;
-        um = __builtin_amdgcn_ballot_w64((uint32_t)b1 < (uint32_t)k.n1) & in2 & vmask & ~rm;
+        const uint64_t in = __builtin_amdgcn_ballot_w64((uint32_t)b1 < (uint32_t)k.n1) & in2 & vmask;
+        um = in & ~rm;
+        if (SPI && !MID) sure = in & ~near1;
         flat = KIND == FCFC_BIN_S ? b1 : (int)__umul24((uint32_t)b1, (uint32_t)k.n2) + b2;
     } else if (!SPI) {
         const float d2c = __builtin_amdgcn_fmed3f(d2, 0.0f, k.vmax1);  // at vmax the table says out of range
@@ -574,8 +580,22 @@ __device__ __attribute__((always_inline)) inline void bin_queue(ArgsRef a, const
         else
             lds_inc(hist_l + ((uint32_t)flat << 2));
     }
-    const uint64_t m = rm;
+    uint64_t m = rm;
     if (m) {
+        if (LIN && SPI && !MID && k.zero2) {
+            // Nothing lies below an edge at 0: a pair near that one only is certain.
+            // (Without this a catalogue in a plane rechecked every pair for its pi = 0:
+            // MI355X, 60,000 points in one plane, 4.11 -> 1.02 ms; 400,000 points at
+            // random 1.14 ms with and without.)
+            const uint64_t z = m & sure & __builtin_amdgcn_ballot_w64(b2f < 1.0f - c.t2);
+            if (__builtin_amdgcn_inverse_ballot_w64(z)) {
+                if (W)
+                    add_weight(s, k.wf, (uint32_t)flat, wa * wb);
+                else
+                    lds_inc(hist_l + ((uint32_t)flat << 2));
+            }
+            m &= ~z;
+        }
         const int pos = c.rcount + (int)lane_prefix(m);
         if (__builtin_amdgcn_inverse_ballot_w64(m)) {
             uint32_t* r = s.rb + (size_t)pos * 2;
@@ -775,6 +795,7 @@ void k_count(const CountArgs* argp) {
     k.l2c = a.l2c;
     k.l2o = a.l2o;
     k.l2t = a.l2t;
+    k.zero2 = a.zero2;
     __asm__ volatile("" : "+s"(k.side32));
     if (LIN) __asm__ volatile("" : "+s"(k.l1c), "+v"(k.l1o), "+s"(k.l1t));
     if (!LIN) __asm__ volatile("" : "+s"(k.scale1), "+s"(k.vmax1));

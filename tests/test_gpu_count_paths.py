@@ -225,3 +225,26 @@ def test_units_of_any_size(kind, los, periodic, p):
         check_case("units, auto", x2 * f, **kw)
         if not periodic:
             check_case("units, tree", x1 * f, x2 * f, tree_leaf=32, **kw)
+
+
+@pytest.mark.parametrize("lo1,lo2", [(0.0, 0.0), (0.0, 2.0), (1.0, 0.0), (0.0, 1e-19), (1e-19, 0.0)])
+@pytest.mark.parametrize("kind,los,tree", [("s", "z", 0), ("spi", "z", 0), ("spi", "z", 64), ("spi", "mid", 0)])
+def test_pairs_on_an_edge_at_zero(kind, los, tree, lo1, lo2):
+    """pi = 0, s_perp = 0 and s = 0 with axes that start at 0 (such a pair is in the
+    first bin), next to 0 and above: points in planes, on lines
+    along z, and twice."""
+    rng = np.random.default_rng(3)
+    n = 1200
+    x = rng.uniform(0, 40.0, (n, 3))
+    x[: n // 2, 2] = np.floor(x[: n // 2, 2] / 10.0) * 10.0
+    x[n // 2: 3 * n // 4, :2] = x[: n // 4, :2]
+    x[-40:] = x[:40]
+    if los == "mid" or tree:
+        x += 200.0
+    e1, e2 = synth.linear_edges(lo1, 12, 8), synth.linear_edges(lo2, 11, 6) if kind == "spi" else None
+    kw = dict(kind=kind, edges1=e1, edges2=e2, los=los, box=0.0 if los == "mid" or tree else 40.0)
+    if tree:
+        kw["tree_leaf"] = tree
+    g, _, st = check_case("edge at zero", x, **kw)
+    if los == "z" and (lo1, lo2) == (0.0, 0.0):
+        assert st["rechecks"] < 0.01 * g.sum()
