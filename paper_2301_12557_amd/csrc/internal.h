@@ -109,10 +109,10 @@ struct Plan {
     Lut1D lut1, lut2;           // s (or s_perp) and pi tables
     Lut1D lut1b, lut2b;         // the same with twice the entries (has_big)
     Lut1D lutbin;               // first-axis table for binning given FP64 values (built on first use)
-    Lut1D luttri;               // table for triangle sides from matrix products
-    Lut1D luttri_n;             // bands for FP32 triangle sides (luttri_e per axis)
+    // triangle sides: tables of 2^14 and 2^13 entries (or of lut_log2) for those from
+    // matrix products, and the bands for FP32 ones (luttri_e per axis)
+    Lut1D luttri[2], luttri_n;
     double luttri_e = 0;
-    int luttri_lg = 0;
     bool has_big = false;       // counts may use the larger tables where LDS allows
     float r2prune32 = 0;        // FP32 candidate threshold (>= every relevant value)
     float d2small = 0;          // pairs closer than this are always rechecked (mu)
@@ -195,8 +195,9 @@ fcfc_status plan_short_tables(const Plan* p, int log2, Lut1D& t1, Lut1D& t2);
 fcfc_status plan_bin_table(Plan* p, const Lut1D** out);
 // Table over the first-axis squared edges for squared lengths formed in FP32
 // from components each within e_axis of their FP64 values (triangle sides);
-// rebuilt when e_axis changes, kept by the plan.
-fcfc_status plan_side_tables(Plan* p, double e_axis, double e_abs, int lg, const Lut1D** wide,
+// rebuilt when e_axis changes, kept by the plan: one of each length that a
+// count tries (slot 0, 1).
+fcfc_status plan_side_tables(Plan* p, double e_axis, double e_abs, int lg, int slot, const Lut1D** wide,
                              const Lut1D** narrow);
 
 // Fixed-point scale 2^S of the exact weighted sums (plan.cpp): every non-zero

@@ -241,26 +241,30 @@ fcfc_status plan_bin_table(Plan* p, const Lut1D** out) {
     return FCFC_OK;
 }
 
-fcfc_status plan_side_tables(Plan* p, double e_axis, double e_abs, int lg, const Lut1D** wide, const Lut1D** narrow) {
-    if (p->luttri.n == 0 || p->luttri_e != e_axis || p->luttri_lg != lg) {
-        // |Q32 - Q64| <= 2 sqrt3 e sqrt(Q) + 3 e^2 + 3.3 u Q for a squared
-        // length formed by an fma chain from FP32 components each within e of
-        // the FP64 ones (the same form as the pair counts' squared separation);
-        // one formed by a matrix product is off by up to e_abs more
-        ErrModel m;
-        m.A = 2.0 * sqrt(3.0) * e_axis;
-        m.B = 3.0 * e_axis * e_axis;
-        m.C = 3.3 * U32 + 1e-15;
-        Lut1D t, tn;
+fcfc_status plan_side_tables(Plan* p, double e_axis, double e_abs, int lg, int slot, const Lut1D** wide,
+                             const Lut1D** narrow) {
+    // |Q32 - Q64| <= 2 sqrt3 e sqrt(Q) + 3 e^2 + 3.3 u Q for a squared
+    // length formed by an fma chain from FP32 components each within e of
+    // the FP64 ones (the same form as the pair counts' squared separation);
+    // one formed by a matrix product is off by up to e_abs more
+    ErrModel m;
+    m.A = 2.0 * sqrt(3.0) * e_axis;
+    m.B = 3.0 * e_axis * e_axis;
+    m.C = 3.3 * U32 + 1e-15;
+    if (p->luttri_n.n == 0 || p->luttri_e != e_axis) {
+        Lut1D tn;
         FCFC_TRY(build_lut(tn, p->e1, m, 8));  // (its bands only)
-        m.B += e_abs;
-        FCFC_TRY(build_lut(t, p->e1, m, lg));
-        p->luttri = t;
         p->luttri_n = tn;
         p->luttri_e = e_axis;
-        p->luttri_lg = lg;
+        p->luttri[0] = p->luttri[1] = Lut1D();
     }
-    *wide = &p->luttri;
+    if (p->luttri[slot].n == 0) {
+        Lut1D t;
+        m.B += e_abs;
+        FCFC_TRY(build_lut(t, p->e1, m, lg));
+        p->luttri[slot] = t;
+    }
+    *wide = &p->luttri[slot];
     *narrow = &p->luttri_n;
     return FCFC_OK;
 }

@@ -818,7 +818,7 @@ extern "C" fcfc_status fcfc_count_triplets(fcfc_plan_t plan, fcfc_cells_t cells,
     int tab_bytes = 0, waves = 0;
     for (int lg = lg0; waves < TRI_MAX_WAVES && lg >= lg1; lg--) {
         const Lut1D *Tp = nullptr, *Tn = nullptr;
-        FCFC_TRY(plan_side_tables(p, e_axis, gram, lg, &Tp, &Tn));
+        FCFC_TRY(plan_side_tables(p, e_axis, gram, lg, lg0 - lg, &Tp, &Tn));
         B = bin_blob(*Tp, blob_h);
         // the narrow bands follow the blob
         std::vector<char> nh;

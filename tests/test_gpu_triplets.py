@@ -298,3 +298,27 @@ def test_very_short_sides(box, edges, nb, weighted):
         ref = oracle.triplets(x, edges=e, box=box)
         assert ref.sum() > 1e5 and ref[:-1].sum() > 1000
         assert_same(got, ref, what="short sides")
+
+
+def test_tables_of_both_lengths_on_one_plan():
+    """Unweighted counts leave room for the longer table, weighted ones for the shorter:
+    the plan keeps both, whichever count comes first."""
+    from paper_2301_12557_amd import fcfc
+    rng = np.random.default_rng(44)
+    e = np.linspace(0.0, 6.0, 19)
+    for first in (False, True):
+        plan = fcfc.Plan("s", e, box=40.0, n_hint=1500)
+        lengths = {}
+        for weighted in (first, not first, first, not first):
+            x = rng.uniform(0, 40, (1500, 3))
+            w = rng.uniform(0.5, 2.0, len(x))
+            cells = plan.build_cells(to_dev(x), to_dev(w))
+            note(f"triplets: one plan, weighted {weighted}")
+            got = plan.count_triplets(cells, weighted=weighted)
+            c, wc = got[0].cpu().numpy(), got[1].cpu().numpy() if weighted else None
+            rc, rw = oracle.triplets(x, edges=e, box=40.0, w=w)
+            assert_same(c, rc, wc, rw if weighted else None, what="one plan")
+            lengths.setdefault(weighted, set()).add(plan.stats()["lut_entries"])
+            cells.close()
+        plan.close()
+        assert all(len(v) == 1 for v in lengths.values()) and max(lengths[False]) > max(lengths[True])
