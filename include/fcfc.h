@@ -439,16 +439,18 @@ fcfc_status fcfc_diag_transcendental(double *rsq_max_rel, double *rcp_max_rel, d
 
 /*
  * fcfc_plan_numerics -- the FP32 constants the counting kernel takes from a
- * plan: the grid its cell-local coordinates are relative to, the candidate
- * threshold, and the bands around bin edges inside which a pair is binned
- * again in FP64 (the single-precision evaluation of the separations of
- * Sect. 2.5 made exact, with the squared-edge bins of Sect. 3.2.1).  Host
+ * plan: the grid its cell-local coordinates are relative to, and the bands
+ * around bin edges inside which a pair is binned again in FP64 (the
+ * single-precision evaluation of the separations of Sect. 2.5 made exact, with
+ * the squared-edge bins of Sect. 3.2.1).  Where bins are read from tables
+ * (fcfc_plan_computed says where not) these are the kernel's tests.  Host
  * only: needs no GPU, so that tests can replay the kernel's FP32 decisions.
  *   nx, ny, nz, cells_per_rmax, lo, side  the grid (lo = 0 in a periodic box)
- *   e_axis     bound on the FP32 error of one displacement component
+ *   e_axis     bound on the FP32 error of one displacement component formed in
+ *              the frame of the A point's cell (computed bins use the frame of a
+ *              tile, with tolerances widened for its span)
  *   side32     FP32 cell side the kernel forms displacements with
- *   r2prune32  a pair is a candidate when its FP32 d2 is below this (every
- *              kind except (s_perp, pi) along z, which tests vmax of both tables)
+ *   r2prune32  no pair that a table could place has an FP32 d2 of this or more
  *   d2small    (s, mu): pairs with FP32 d2 below this are always rechecked
  *   mu_tolA, mu_tolC  (s, mu): a pair whose FP32 mu*n2 lies closer than
  *              mu_tolA * rsq(d2) + mu_tolC to an interior mu edge is rechecked
@@ -466,6 +468,36 @@ typedef struct fcfc_numerics {
     int32_t reserved;
 } fcfc_numerics;
 fcfc_status fcfc_plan_numerics(fcfc_plan_t plan, fcfc_numerics *out);
+
+/*
+ * fcfc_plan_computed -- the constants of computed bins: where the edges of every
+ * axis are uniform (within 1e-9 of a bin) the counting kernel forms a pair's bin
+ * from the hardware reciprocal square root and reads no table.  Host only, for
+ * the same use as fcfc_plan_numerics.
+ *   uniform    1: bins are computed; 0: tables are read (the rest is then zero)
+ *   zero2      the second axis starts at 0: nothing lies below that edge
+ *   scale1, offset1  the first axis: x = fma(v rsq(v), scale1, offset1) for the
+ *              squared separation v (its transverse part for (s_perp, pi)) is the
+ *              bin plus a fraction
+ *   tol1, tol1_abs   a pair with |x - rint(x)| below tol1 (for (s_perp, pi) to the
+ *              mid-point tol1 + tol1_abs rsq(v)) is binned again in FP64
+ *   scale2, offset2, tol2  the same for |pi| of (s_perp, pi)
+ *   mu_n       (s, mu): mu n2 is formed with this, a little below n2
+ *   mu_tolA, mu_tolC  (s, mu): a pair closer to an interior mu edge than
+ *              mu_tolA rsq(d2) + mu_tolC is binned again in FP64
+ *   reach, e_unit    in a grid the tolerances are multiplied by max(1, e_unit (16
+ *              side32 + 6 span + 4.1 reach)) for a tile that spans `span` along x,
+ *              whose first cell is the origin of the pair's x coordinates
+ * Errors: FCFC_EINVAL (null), FCFC_ESTATE (open box before its bounds are set).
+ */
+typedef struct fcfc_computed {
+    int32_t uniform, zero2;
+    float scale1, offset1, tol1, tol1_abs;
+    float scale2, offset2, tol2;
+    float mu_n, mu_tolA, mu_tolC;
+    float reach, e_unit;
+} fcfc_computed;
+fcfc_status fcfc_plan_computed(fcfc_plan_t plan, fcfc_computed *out);
 
 /*
  * fcfc_plan_table -- copy one of a plan's squared-separation look-up tables

@@ -150,6 +150,19 @@ static void set_linear(const Plan* p, CountArgs& a) {
     if (!(a.l1t < 0.25f) || (two && !(a.l2t < 0.25f))) a.lin = 0;
 }
 
+// The mu axis: what mu n2 is formed with, and its band around interior edges.
+static void set_mu(const Plan* p, bool lin, CountArgs& a) {
+    const float shrink = mu_shrink(p->los == FCFC_LOS_MIDPOINT);
+    a.mu_n = (float)p->n2;
+    a.mu_c = lin ? a.mu_n * (1.0f - shrink) : a.mu_n;
+    // one mu bin has no interior edge: nothing is near one
+    a.tolA = a.tolC = 0.0f;
+    if (p->kind != FCFC_BIN_S_MU || p->n2 < 2) return;
+    // pairs closer than sqrt(d2small) are always rechecked: the band then spans a whole mu bin
+    a.tolA = std::max(p->mu_tolA, 1.01f * sqrtf(p->d2small));
+    a.tolC = p->mu_tolC + (lin ? 1.01f * shrink * a.mu_n : 0.0f);
+}
+
 // Format of the weighted words (add_weight) for products p with p 2^S integer
 // and |p| <= pmax.  A wave may test `limit` pairs and one more batch (at most
 // 79 staged B points x 64, and the rechecks waiting) before the words have to
@@ -356,11 +369,7 @@ static fcfc_status setup_launch(Plan* p, bool is_auto, bool weighted, bool batch
     a.side32 = (float)g.side;
     a.L = g.L;
     a.halfL = g.L * 0.5;
-    a.mu_n = (float)p->n2;
-    a.mu_c = a.mu_n * (1.0f - mu_shrink(p->los == FCFC_LOS_MIDPOINT));
-    // pairs closer than sqrt(d2small) are always rechecked: the band then spans a whole mu bin
-    a.tolA = std::max(p->mu_tolA, 1.01f * sqrtf(p->d2small));
-    a.tolC = p->mu_tolC;
+    set_mu(p, lin, a);
     a.mu_top_closed = 1;
     set_filter(p, a);
     set_linear(p, a);
@@ -1235,3 +1244,39 @@ fcfc_status batch_stats_impl(BatchImpl* b, hipStream_t st, int64_t out[3]) {
 }
 
 }  // namespace fcfc
+
+using namespace fcfc;
+
+extern "C" fcfc_status fcfc_plan_computed(fcfc_plan_t plan, fcfc_computed* out) {
+    clear_error();
+    const Plan* p = (const Plan*)plan;
+    if (!p || !out) return FCFC_EINVAL;
+    if (!p->numerics_ready) {
+        set_error("plan_computed: the grid is not fixed yet (set or fit the bounds first)");
+        return FCFC_ESTATE;
+    }
+    CountArgs a;
+    memset(&a, 0, sizeof(a));
+    set_linear(p, a);
+    fcfc_computed c{};
+    if (a.lin) {
+        set_mu(p, true, a);
+        set_filter(p, a);
+        c.uniform = 1;
+        c.zero2 = a.zero2;
+        c.scale1 = a.l1c;
+        c.offset1 = a.l1o;
+        c.tol1 = a.l1t;
+        c.tol1_abs = p->kind == FCFC_BIN_SPERP_PI && p->los == FCFC_LOS_MIDPOINT ? a.l1a : 0.0f;
+        c.scale2 = a.l2c;
+        c.offset2 = a.l2o;
+        c.tol2 = a.l2t;
+        c.mu_n = a.mu_c;
+        c.mu_tolA = a.tolA;
+        c.mu_tolC = a.tolC;
+        c.reach = a.f_reach;
+        c.e_unit = a.e_unit;
+    }
+    *out = c;
+    return FCFC_OK;
+}

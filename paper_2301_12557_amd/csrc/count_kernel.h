@@ -126,7 +126,7 @@ struct CountArgs {
     int zero2;  // the second axis starts at 0
     float e_unit;  // u over the error of one displacement component
     float xstep;   // a row's points are sorted by x to this
-    float mu_n, mu_c, tolA, tolC;  // mu_c: mu_n less mu_shrink
+    float mu_n, mu_c, tolA, tolC;  // mu_c: what mu n2 is formed with (set_mu)
     int mu_top_closed;
     WeightFmt wf;
     int copies;
@@ -773,11 +773,10 @@ void k_count(const CountArgs* argp) {
     k.scale2 = a.scale2;
     k.vmax1 = a.vmax1;
     k.vmax2 = a.vmax2;
-    k.mu_n = LIN ? a.mu_c : a.mu_n;
+    k.mu_n = a.mu_c;
     k.mu_nm1 = a.mu_n - 1.0f;
-    // one mu bin has no interior edge: nothing is near one
-    k.tolA = a.n2 > 1 ? a.tolA : 0.0f;
-    k.tolC = a.n2 > 1 ? a.tolC + (LIN ? 1.01f * mu_shrink(MID) * a.mu_n : 0.0f) : 0.0f;
+    k.tolA = a.tolA;
+    k.tolC = a.tolC;
     k.tolC_v = k.tolC;
     __asm__ volatile("" : "+v"(k.tolC_v));
     k.side32 = a.side32;

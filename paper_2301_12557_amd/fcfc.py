@@ -67,6 +67,12 @@ class Numerics(ctypes.Structure):
                 ("trans_rel", ctypes.c_float), ("has_big", ctypes.c_int32), ("reserved", ctypes.c_int32)]
 
 
+class Computed(ctypes.Structure):
+    _fields_ = [("uniform", ctypes.c_int32), ("zero2", ctypes.c_int32)] + \
+               [(k, ctypes.c_float) for k in ("scale1", "offset1", "tol1", "tol1_abs", "scale2", "offset2", "tol2",
+                                              "mu_n", "mu_tolA", "mu_tolC", "reach", "e_unit")]
+
+
 # (name, restype, argtypes) of every exported entry point of include/fcfc.h
 _P = ctypes.c_void_p
 _I32 = ctypes.c_int32
@@ -82,6 +88,7 @@ SIGNATURES = [
     ("fcfc_noalloc_scratch_bytes", _I64, []),
     ("fcfc_plan_stats", _I32, [_P, ctypes.POINTER(Stats)]),
     ("fcfc_plan_numerics", _I32, [_P, ctypes.POINTER(Numerics)]),
+    ("fcfc_plan_computed", _I32, [_P, ctypes.POINTER(Computed)]),
     ("fcfc_plan_table", _I32, [_P, _I32, _P, _P, _P, _P, _I64, ctypes.POINTER(_I64), ctypes.POINTER(ctypes.c_float),
                                ctypes.POINTER(ctypes.c_float)]),
     ("fcfc_weight_scale", _I32, [_D, _D, _D, _D, _I32, ctypes.POINTER(_I32)]),
@@ -315,6 +322,12 @@ class Plan:
         d = {k: getattr(n, k) for k, _ in Numerics._fields_ if k != "reserved"}
         d["lo"] = list(n.lo)
         return d
+
+    def computed(self):
+        """The constants of computed bins (fcfc_plan_computed), as a dict."""
+        c = Computed()
+        check(load().fcfc_plan_computed(self.h, ctypes.byref(c)))
+        return {k: getattr(c, k) for k, _ in Computed._fields_}
 
     def table(self, which):
         """Look-up table `which` (0: s or s_perp, 1: pi, 2 and 3: the same with twice
