@@ -1044,6 +1044,8 @@ void k_count(const CountArgs* argp) {
         const float selside = (!TREE && !LIN && lk == 0) ? k.side32 : 0.f;
         const float off_k = sig * (lk == 0 ? -cx : (lk == 1 ? (TREE ? 0.f : Dy) - cy : (TREE ? 0.f : Dz) - cz));
         const float F_k = lk == 0 ? Fx : (lk == 1 ? Fy : Fz);
+        float sigv = sig;
+        if (W) __asm__ volatile("" : "+v"(sigv));  // (weighted counts have vector registers to spare)
         int ns = 0;  // staged B points waiting
         for (;;) {
             // ---- cull and stage the next 64 B points ----
@@ -1132,7 +1134,7 @@ void k_count(const CountArgs* argp) {
                 float v = lds_f1(sat + 4u * (uint32_t)lk);
                 const uint32_t w = __float_as_uint(lds_f1(sat + 12u));
                 if (!TREE && !LIN) v = __builtin_fmaf((float)(w & 255u) - 64.0f, selside, v);
-                v = __builtin_fmaf(v, sig, off_k);
+                v = __builtin_fmaf(v, sigv, off_k);
                 // slots past the last staged point (stale memory) become the origin with
                 // a |b|^2 out of every reach
                 const bool staged = slot < ns;
