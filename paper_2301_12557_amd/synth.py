@@ -215,16 +215,17 @@ def _running_sum_torch(rho, ncol):
     changed 13 of 50 bins of a count of 10 million).  Here rows of ncol are summed
     each by itself, in a fixed order, and the sums of the rows are added up as whole
     numbers (two of them: multiples of 2^-36 of the largest row, and the rest), which
-    no order changes.  256^3 values on MI355X: 0.23 ms, torch.cumsum 0.07."""
+    no order changes.  256^3 values on MI355X: 0.18 ms, torch.cumsum 0.07."""
     import torch
     rows = torch.cumsum(rho.reshape(-1, ncol), 1)
     tot = rows[:, -1]
-    big = float(np.ldexp(1.0, int(np.frexp(float(tot.max()))[1]) - 36))
-    small = big * 2.0 ** -40
-    hi = torch.floor(tot / big)
-    lo = torch.floor((tot - hi * big) / small)
+    scale = torch.exp2((36 - torch.frexp(tot.max())[1]).double())
+    t = tot * scale
+    hi = torch.floor(t)
+    whole = torch.cumsum(hi.long(), 0).double()
+    rest = torch.cumsum(((t - hi) * 2.0 ** 40).long(), 0).double()
     before = torch.zeros_like(tot)
-    before[1:] = (torch.cumsum(hi.long(), 0).double() * big + torch.cumsum(lo.long(), 0).double() * small)[:-1]
+    torch.div(torch.add(whole, rest, alpha=2.0 ** -40)[:-1], scale, out=before[1:])
     return (rows + before[:, None]).reshape(-1)
 
 
