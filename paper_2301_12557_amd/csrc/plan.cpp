@@ -211,7 +211,7 @@ static fcfc_status build_lut(Lut1D& t, const std::vector<double>& edges, const E
     // the entries that meet a band hold its code, the first band's where
     // several meet one entry (written last).  Runs are filled whole: a test of
     // every edge for every entry took half of a small count (20,000 points in
-    // 20 bins: plan 0.46 -> 0.01 ms).
+    // 40 bins: plan 0.46 -> 0.01 ms).
     t.tab.assign((size_t)nt, LUT_NONE);
     auto entry = [&](double x) { return (int64_t)std::min(std::max(x, 0.0), (double)nt); };
     for (int k = 0; k < t.n; k++)
